@@ -15,6 +15,7 @@
 
 #include "lattice.h"
 #include "runtime.h"
+#include "twostep.h"
 
 namespace {
 
@@ -168,6 +169,18 @@ int require_ready(lbm_handle* h) {
   if (!h) return fail(LBM_EINVAL, "handle is NULL");
   if (!h->initialised) return fail(LBM_ESTATE, "state not initialised (call lbm_init_*)");
   return LBM_OK;
+}
+
+// Whether steps go two at a time. 16-bit storage keeps single steps: its
+// kernels are bound by the vector units, and the ring of the two-step tile would
+// be computed on top (FP16 1024 x 64 x 128: 209 us single, 249 paired); so does
+// the 54-population model in FP64, whose nodes in flight do not fit the
+// registers.
+bool two_steps(const lbm_handle* h) {
+  const lbm_config& c = h->cfg;
+  if (c.storage != LBM_F32 && (c.storage != LBM_F64 || c.model == LBM_CUMULANT27_FCM27)) return false;
+  const lbm::Grid g{c.nx, c.ny, c.nz, h->n, lbm::xblocks(c.nx)};
+  return lbm::two_step_pays(g, h->qt, (int)h->esize, h->cu_count);
 }
 
 int set_device(lbm_handle* h) {
@@ -484,6 +497,7 @@ int lbm_create(const lbm_config* cfg, void* dev_workspace, size_t bytes, void* h
   h->scratch = (double*)(h->ws + L.scratch);
   h->diag_blocks = L.diag_blocks;
   h->step = 0;
+  h->per_launch = 1;
   h->initialised = false;
   h->x0 = (int)floor(0.125 * cfg->nx);
   *out = h;
@@ -547,11 +561,15 @@ int lbm_step(lbm_handle* h, int64_t n) {
   if (n == 0) return LBM_OK;
   rc = set_device(h);
   if (rc) return rc;
-  for (int64_t i = 0; i < n; ++i) {
+  const bool pairs = two_steps(h);
+  for (int64_t i = 0; i < n;) {
+    h->per_launch = pairs && n - i >= 2 ? 2 : 1;
     HIPCHECK(lbm::launch_step(h, h->buf[h->cur], h->buf[h->cur ^ 1]));
     h->cur ^= 1;
-    h->step += 1;
+    h->step += h->per_launch;
+    i += h->per_launch;
   }
+  h->per_launch = 1;
   return LBM_OK;
 }
 

@@ -1,5 +1,5 @@
-// Forward kernels: fused gather + collide + store step, initial states,
-// moment export, FP64 diagnostics, test hooks.
+// Forward kernels besides the step: initial states, moment export, FP64
+// diagnostics, test hooks.
 //
 // State convention. A population buffer holds post-collision values at the
 // node where they were produced. One step pulls them (the gather with
@@ -14,29 +14,9 @@
 #include <algorithm>
 #include <mutex>
 
-#include "collide.h"
-#include "lattice.h"
-#include "runtime.h"
+#include "dispatch.h"
 
 namespace lbm {
-
-template <int MODEL>
-struct ModelT;
-template <>
-struct ModelT<0> {
-  using LF = Q27;
-  using LS = Q7;
-};
-template <>
-struct ModelT<1> {
-  using LF = Q19;
-  using LS = Q6;
-};
-template <>
-struct ModelT<2> {
-  using LF = Q27;
-  using LS = Q27;
-};
 
 template <typename T>
 LBM_HD double to_d(T v);
@@ -44,110 +24,6 @@ template <>
 LBM_HD double to_d<double>(double v) { return v; }
 template <>
 LBM_HD double to_d<float>(float v) { return (double)v; }
-
-// Post-collision values are not read again before the next launch, so they
-// may bypass the caches on the way to HBM (plain stores measured 5 % slower).
-template <typename ST>
-__device__ __forceinline__ void store_val(ST* p, ST v) {
-  if constexpr (std::is_same<ST, double>::value || std::is_same<ST, float>::value) {
-    __builtin_nontemporal_store(v, p);
-  } else {
-    uint16_t bits;
-    __builtin_memcpy(&bits, &v, 2);
-    __builtin_nontemporal_store(bits, reinterpret_cast<uint16_t*>(p));
-  }
-}
-
-// ------------------------------------------------------------------- step
-// collision kinds of the cumulant models
-enum { kCumFast = 0, kCumGeneral = 1, kCumParam = 2 };
-
-// one tile: NPT * blockDim.x consecutive nodes of one row; KIND: kCumFast
-// (omega3..omega6 = 1), kCumGeneral (given rates), kCumParam (parametrised).
-// FW (the adjoint's forward pass): the tiles of the wall layers z = 0, 1 also
-// write the x-velocity sums of their x-blocks that F_w (Eq. 62, 64) needs for
-// the state they gather, as the separate wall-layer kernel does: per x-block
-// the wave sum of u_x = j_x / rho (FP64, populations in order) into
-// fwp[2 b + z], with b = xb + nxb (y + ny z), and 0 into the other slot.
-template <int MODEL, typename ST, typename SS, typename CT, bool LES, int KIND, int NPT,
-          bool FW = false>
-__device__ __forceinline__ void step_tile(const ST* __restrict__ src, ST* __restrict__ dst,
-                                          const Grid& g, const Phys<CT>& p, int nbx, int b,
-                                          double* __restrict__ fwp) {
-  using LF = typename ModelT<MODEL>::LF;
-  using LS = typename ModelT<MODEL>::LS;
-  const int row = b / nbx;
-  const int x0 = (b - row * nbx) * (int)blockDim.x * NPT;
-  // lanes with no node at all; the wave sums of FW need every lane of a wave
-  if (!FW && x0 + (int)threadIdx.x >= g.nx) return;
-  const int y = row % g.ny, z = row / g.ny;
-  constexpr int QT = LF::Q + LS::Q;
-  const TileLanes<QT, NPT> t = tile_lanes<QT, NPT>(g, x0, (int)threadIdx.x, (int)blockDim.x);
-  CT fg[NPT][LF::Q], ph[NPT][LS::Q];
-  gather_rows<LF, LS, NPT, ST, CT, SS>(src, g, t, y, z, fg, ph);
-  if constexpr (FW) {
-    if (z < 2) {  // uniform per block
-      const int wave = (int)threadIdx.x >> 6, lane = (int)threadIdx.x & 63;
-#pragma unroll
-      for (int k = 0; k < NPT; ++k) {
-        double v = 0.0;
-        if (t.x[k] < g.nx) {
-          double drho = 0.0, jx = 0.0;
-          static_for<0, LF::Q>([&](auto qc) {
-            constexpr int q = decltype(qc)::value;
-            drho += (double)fg[k][q];
-            if (LF::cx[q]) jx += LF::cx[q] * (double)fg[k][q];
-          });
-          v = jx / (1.0 + drho);
-        }
-        for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-        const int xb = ((x0 + k * (int)blockDim.x) >> kXBShift) + wave;
-        if (lane == 0 && xb < g.nxb) {
-          const int64_t fb = xb + (int64_t)g.nxb * (y + (int64_t)g.ny * z);
-          fwp[2 * fb] = z == 0 ? v : 0.0;
-          fwp[2 * fb + 1] = z == 0 ? 0.0 : v;
-        }
-      }
-    }
-  }
-#pragma unroll
-  for (int k = 0; k < NPT; ++k) {
-    if constexpr (MODEL == 0 || MODEL == 2) {
-      if constexpr (KIND == kCumParam)
-        collide_cumulant27_param<LS, CT>(fg[k], ph[k], p);
-      else if constexpr (KIND == kCumGeneral)
-        collide_cumulant27_general<LS, LES, CT>(fg[k], ph[k], p);
-      else
-        collide_cumulant27<LS, LES, CT>(fg[k], ph[k], p);
-    } else {
-      collide_bgk_q19_q6<LES, CT>(fg[k], ph[k], p);
-    }
-  }
-  // block-uniform segment pointers + the lane's own offset, as for the loads
-  ST* drow = dst + (int64_t)row * g.nxb * (QT * kXB);
-  static_for<0, QT>([&](auto qc) {
-    constexpr int a = decltype(qc)::value;
-    ST* pa = drow + a * kXB;
-#pragma unroll
-    for (int k = 0; k < NPT; ++k) {
-      if ((k == 0 && !FW) || t.x[k] < g.nx) {
-        if constexpr (a < LF::Q)
-          store_val(&pa[t.own[k]], Conv<ST, CT>::store(fg[k][a]));
-        else
-          store_val(&reinterpret_cast<SS*>(pa)[t.own[k]], Conv<SS, CT>::store(ph[k][a - LF::Q]));
-      }
-    }
-  });
-}
-
-template <int MODEL, typename ST, typename SS, typename CT, bool LES, int KIND, int NPT,
-          bool FW = false>
-__global__ __launch_bounds__(kBlock) void k_step(const ST* __restrict__ src, ST* __restrict__ dst,
-                                                 Grid g, Phys<CT> p, int nbx,
-                                                 double* __restrict__ fwp) {
-  step_tile<MODEL, ST, SS, CT, LES, KIND, NPT, FW>(src, dst, g, p, nbx,
-                                                   xcd_row_order(blockIdx.x, gridDim.x, nbx), fwp);
-}
 
 // ------------------------------------------------------------ init states
 __device__ __forceinline__ uint64_t splitmix64(uint64_t x) {
@@ -559,150 +435,9 @@ hipError_t static_scratch(double** ptr) {
 }
 
 // ---------------------------------------------------------------- dispatch
-static Grid grid_of(const lbm_handle* h) {
-  return Grid{h->cfg.nx, h->cfg.ny, h->cfg.nz, h->n, xblocks(h->cfg.nx)};
-}
-
 static int block_x(const lbm_handle* h) {
   const int nx = h->cfg.nx;
   return nx >= kBlock ? kBlock : ((nx + 63) / 64) * 64;
-}
-
-template <typename CT>
-static Phys<CT> phys_of(const lbm_handle* h) {
-  const lbm_params& p = h->prm;
-  const lbm_config& c = h->cfg;
-  Phys<CT> r;
-  r.g = (CT)p.g_prime;
-  r.tau0 = (CT)p.tau0;
-  r.tau_phi0 = (CT)p.tau_phi0;
-  // 18 sqrt(2) C_s^2 (standard closure) or 18 sqrt(2) C_s (as printed in Eq. 32)
-  r.c_les = (CT)(18.0 * sqrt(2.0) * (c.smag_paper_form ? c.cs_smag : c.cs_smag * c.cs_smag));
-  r.d0 = (CT)p.d0;
-  r.inv_sct = (CT)(1.0 / c.sc_t);
-  r.inv_cs2phi = (CT)(1.0 / p.cs2_phi);
-  r.omega2 = (CT)c.omega_bulk;
-  r.omega3 = (CT)c.omega3;
-  r.omega4 = (CT)c.omega4;
-  r.omega5 = (CT)c.omega5;
-  r.omega6 = (CT)c.omega6;
-  const double h4 = p.tau0 - 0.5;  // 1/omega1 - 1/2
-  r.w_plus = (CT)p.w_plus;
-  r.w_minus = (CT)p.w_minus;
-  r.w_111 = (CT)p.w_111;
-  r.a4 = (CT)(-2.0 / 3.0 * h4 * p.coef_a);
-  r.b4 = (CT)(-1.0 / 3.0 * h4 * p.coef_b);
-  r.lam = c.limiter > 0.0 ? (CT)c.limiter : (CT)INFINITY;
-  return r;
-}
-
-// calls f(ST{}, SS{}, CT{}) for the handle's storage mode: flow element
-// type, scalar element type, arithmetic type
-template <class F>
-static hipError_t with_storage(const lbm_handle* h, F&& f) {
-  switch (h->cfg.storage) {
-    case LBM_F64: return f(double{}, double{}, double{});
-    case LBM_F32: return f(float{}, float{}, float{});
-    case LBM_F16: return f(__half{}, __half{}, float{});
-    case LBM_BF16: return f(bf16_t{}, bf16_t{}, float{});
-    case LBM_BF16_F16S: return f(bf16_t{}, __half{}, float{});
-  }
-  return hipErrorInvalidValue;
-}
-template <class F>
-static hipError_t with_model(const lbm_handle* h, F&& f) {
-  switch (h->cfg.model) {
-    case LBM_CUMULANT27_Q7: return f(std::integral_constant<int, 0>{});
-    case LBM_BGK19_SMAG_Q6: return f(std::integral_constant<int, 1>{});
-    case LBM_CUMULANT27_FCM27: return f(std::integral_constant<int, 2>{});
-  }
-  return hipErrorInvalidValue;
-}
-
-static int cumulant_kind(const lbm_handle* h) {
-  const lbm_config& c = h->cfg;
-  if (c.parametrized) return kCumParam;
-  return (c.omega3 != 1.0 || c.omega4 != 1.0 || c.omega5 != 1.0 || c.omega6 != 1.0) ? kCumGeneral
-                                                                                   : kCumFast;
-}
-
-template <int M, typename ST, typename SS, typename CT, int NPT>
-static hipError_t launch_step_npt(lbm_handle* h, const Grid& g, const void* src, void* dst,
-                                  double* fw, hipStream_t st) {
-  const bool les = h->cfg.cs_smag > 0.0;
-  const int per_thread_x = (g.nx + NPT - 1) / NPT;  // x-extent in threads if one block
-  const int bx = per_thread_x >= kBlock ? kBlock : ((per_thread_x + 63) / 64) * 64;
-  const int nbx = (g.nx + bx * NPT - 1) / (bx * NPT);
-  const unsigned blocks = (unsigned)((int64_t)nbx * g.ny * g.nz);
-  const Phys<CT> p = phys_of<CT>(h);
-  const ST* s = static_cast<const ST*>(src);
-  ST* d = static_cast<ST*>(dst);
-  if (fw) {  // the adjoint's forward pass: FP32 / FP64 storage
-    if constexpr (std::is_same<ST, CT>::value && std::is_same<SS, ST>::value) {
-      const int kind = M == 1 ? kCumFast : cumulant_kind(h);
-      if (kind == kCumGeneral) return hipErrorInvalidValue;
-      if constexpr (M != 1) {
-        if (kind == kCumParam) {
-          hipLaunchKernelGGL((k_step<M, ST, SS, CT, false, kCumParam, NPT, true>), dim3(blocks), dim3(bx), 0, st, s, d, g, p, nbx, fw);
-          return hipGetLastError();
-        }
-      }
-      if (les)
-        hipLaunchKernelGGL((k_step<M, ST, SS, CT, true, kCumFast, NPT, true>), dim3(blocks), dim3(bx), 0, st, s, d, g, p, nbx, fw);
-      else
-        hipLaunchKernelGGL((k_step<M, ST, SS, CT, false, kCumFast, NPT, true>), dim3(blocks), dim3(bx), 0, st, s, d, g, p, nbx, fw);
-      return hipGetLastError();
-    } else {
-      return hipErrorInvalidValue;
-    }
-  }
-  if constexpr (M == 1) {  // BGK: one collision kind
-    if (les)
-      hipLaunchKernelGGL((k_step<M, ST, SS, CT, true, kCumFast, NPT>), dim3(blocks), dim3(bx), 0, st, s, d, g, p, nbx, nullptr);
-    else
-      hipLaunchKernelGGL((k_step<M, ST, SS, CT, false, kCumFast, NPT>), dim3(blocks), dim3(bx), 0, st, s, d, g, p, nbx, nullptr);
-  } else {
-    // the parametrised kind never has the LES (rejected when the handle is made)
-    const int kind = cumulant_kind(h);
-    if (les && kind == kCumGeneral)
-      hipLaunchKernelGGL((k_step<M, ST, SS, CT, true, kCumGeneral, NPT>), dim3(blocks), dim3(bx), 0, st, s, d, g, p, nbx, nullptr);
-    else if (les)
-      hipLaunchKernelGGL((k_step<M, ST, SS, CT, true, kCumFast, NPT>), dim3(blocks), dim3(bx), 0, st, s, d, g, p, nbx, nullptr);
-    else if (kind == kCumParam)
-      hipLaunchKernelGGL((k_step<M, ST, SS, CT, false, kCumParam, NPT>), dim3(blocks), dim3(bx), 0, st, s, d, g, p, nbx, nullptr);
-    else if (kind == kCumGeneral)
-      hipLaunchKernelGGL((k_step<M, ST, SS, CT, false, kCumGeneral, NPT>), dim3(blocks), dim3(bx), 0, st, s, d, g, p, nbx, nullptr);
-    else
-      hipLaunchKernelGGL((k_step<M, ST, SS, CT, false, kCumFast, NPT>), dim3(blocks), dim3(bx), 0, st, s, d, g, p, nbx, nullptr);
-  }
-  return hipGetLastError();
-}
-
-// Grids too small to give every SIMD four waves at the preferred nodes per
-// thread (cache-resident, latency-bound runs such as a 256 x 16 x 32
-// adjoint) take one node per thread: twice the waves.
-static bool few_waves(const lbm_handle* h, int npt) {
-  const int64_t waves = (h->n + (int64_t)64 * npt - 1) / ((int64_t)64 * npt);
-  return waves < (int64_t)16 * h->cu_count;
-}
-
-hipError_t launch_step(lbm_handle* h, const void* src, void* dst, double* fw,
-                       hipStream_t stream) {
-  const Grid g = grid_of(h);
-  if (!stream) stream = h->stream;
-  return with_model(h, [&](auto mc) {
-    constexpr int M = decltype(mc)::value;
-    return with_storage(h, [&](auto st, auto ss, auto ct) {
-      using ST = decltype(st);
-      using SS = decltype(ss);
-      using CT = decltype(ct);
-      constexpr int NPT = nodes_per_thread<M, ST>();
-      if constexpr (NPT > 1) {
-        if (few_waves(h, NPT)) return launch_step_npt<M, ST, SS, CT, 1>(h, g, src, dst, fw, stream);
-      }
-      return launch_step_npt<M, ST, SS, CT, NPT>(h, g, src, dst, fw, stream);
-    });
-  });
 }
 
 template <class Init>

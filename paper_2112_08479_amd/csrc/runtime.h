@@ -29,6 +29,7 @@ struct lbm_handle {
   double* d0;         // 8 doubles: diagnostics at initialisation
   double* scratch;    // n doubles (get/set hooks)
   int64_t step;
+  int per_launch;     // steps that the next launch_step makes: 1 or 2
   bool initialised;
   int x0;             // gate index
   int diag_blocks;
@@ -52,13 +53,42 @@ constexpr int nodes_per_thread() {
 }
 constexpr int kDiagSlots = 8;  // partial sums per diagnostic block
 
-// kernels.hip
+// step.cpp
 // one step src -> dst; fw (the adjoint's forward pass, FP32 / FP64 storage):
 // also the wall-layer sums of F_w of the gathered state into
 // fw[2 fw_blocks], as launch_fw_layers writes them. st: the stream to launch
-// on (null: the handle's)
+// on (null: the handle's). With h->per_launch = 2 and no fw the launch makes two
+// steps, with the bits of two single ones.
 hipError_t launch_step(lbm_handle* h, const void* src, void* dst, double* fw = nullptr,
                        hipStream_t st = nullptr);
+hipError_t launch_step_fw(lbm_handle* h, const void* src, void* dst, double* fw, hipStream_t st);
+// by model: step_m*.hip, step16_m*.hip
+template <int MODEL>
+hipError_t launch_step_real(lbm_handle* h, const void* src, void* dst, hipStream_t st);
+template <int MODEL>
+hipError_t launch_step2_real(lbm_handle* h, const void* src, void* dst, hipStream_t st);
+template <int MODEL>
+hipError_t launch_step_16(lbm_handle* h, const void* src, void* dst, hipStream_t st);
+template <>
+hipError_t launch_step_real<0>(lbm_handle*, const void*, void*, hipStream_t);
+template <>
+hipError_t launch_step_real<1>(lbm_handle*, const void*, void*, hipStream_t);
+template <>
+hipError_t launch_step_real<2>(lbm_handle*, const void*, void*, hipStream_t);
+template <>
+hipError_t launch_step2_real<0>(lbm_handle*, const void*, void*, hipStream_t);
+template <>
+hipError_t launch_step2_real<1>(lbm_handle*, const void*, void*, hipStream_t);
+template <>
+hipError_t launch_step2_real<2>(lbm_handle*, const void*, void*, hipStream_t);
+template <>
+hipError_t launch_step_16<0>(lbm_handle*, const void*, void*, hipStream_t);
+template <>
+hipError_t launch_step_16<1>(lbm_handle*, const void*, void*, hipStream_t);
+template <>
+hipError_t launch_step_16<2>(lbm_handle*, const void*, void*, hipStream_t);
+
+// kernels.hip
 hipError_t launch_init_lock(lbm_handle* h, double lock_fraction, double amp, uint64_t seed);
 hipError_t launch_init_field(lbm_handle* h, const double* chi0);
 hipError_t launch_moments(lbm_handle* h, int dtype, void* rho, void* ux, void* uy, void* uz,
