@@ -60,7 +60,6 @@ size_t state_bytes_of(const lbm_config* c, int qt) {
 
 struct Layout {
   size_t buf, chibar, partials, dres, d0, scratch, total;
-  int diag_blocks;
 };
 
 int block_x(int nx) { return nx >= lbm::kBlock ? lbm::kBlock : ((nx + 63) / 64) * 64; }
@@ -69,14 +68,12 @@ Layout layout_of(const lbm_config* c, const lbm_params* p) {
   Layout L;
   const int64_t n = (int64_t)c->nx * c->ny * c->nz;
   const int qt = p->q_flow + p->q_scalar;
-  const int nbx = (c->nx + block_x(c->nx) - 1) / block_x(c->nx);
-  L.diag_blocks = nbx * c->nz;
   size_t off = 0;
   L.buf = align256(state_bytes_of(c, qt) + lbm::kBufferGuardBytes);
   L.chibar = 2 * L.buf;
   off = L.chibar + align256((size_t)c->nx * c->nz * sizeof(double));
   L.partials = off;
-  off += align256((size_t)L.diag_blocks * lbm::kDiagSlots * sizeof(double));
+  off += align256(lbm::diag_partials(c->nx, lbm::xblocks(c->nx), c->nz) * sizeof(double));
   L.dres = off;
   off += 256;
   L.d0 = off;
@@ -310,7 +307,6 @@ int lbm_adjoint_run(lbm_handle* h, int64_t n_steps, int64_t k_ckpt, double w_fro
   double* fwpart = (double*)(ws + L.fwpart);
   double* small = (double*)(ws + L.small);  // [0] F_w sum, [8..12] front seed, [16..17] params
   const int nblk = lbm::adjoint_blocks(h);
-  const size_t sbytes = h->state_bytes;
   auto ckpt = [&](int64_t s) { return (void*)(ws + L.ckpt + (size_t)s * L.buf); };
   HIPCHECK(lbm::launch_zero(h, gpart, 2 * (int64_t)nblk));
   HIPCHECK(lbm::launch_zero(h, small, 32));
@@ -345,7 +341,7 @@ int lbm_adjoint_run(lbm_handle* h, int64_t n_steps, int64_t k_ckpt, double w_fro
   // whatever the checkpoint interval.
   const int fwb = lbm::fw_blocks(h);
   double* fw_spare = fwpart + 2 * (size_t)fwb * n_steps;
-  HIPCHECK(hipMemcpyAsync(ckpt(0), h->buf[h->cur], sbytes, hipMemcpyDeviceToDevice, h->stream));
+  HIPCHECK(lbm::launch_copy_state(h, h->buf[h->cur], ckpt(0)));
   const void* cur = ckpt(0);
   for (int64_t m = 0; m < n_steps; ++m) {
     const int64_t mn = m + 1;
@@ -495,7 +491,6 @@ int lbm_create(const lbm_config* cfg, void* dev_workspace, size_t bytes, void* h
   h->dres = (double*)(h->ws + L.dres);
   h->d0 = (double*)(h->ws + L.d0);
   h->scratch = (double*)(h->ws + L.scratch);
-  h->diag_blocks = L.diag_blocks;
   h->step = 0;
   h->per_launch = 1;
   h->initialised = false;
@@ -527,7 +522,7 @@ int lbm_destroy(lbm_handle* h) {
 static int after_init(lbm_handle* h) {
   h->step = 0;
   h->initialised = true;
-  return run_diag(h, h->d0);
+  return LBM_OK;
 }
 
 int lbm_init_lock_exchange(lbm_handle* h, double lock_fraction, double noise_amp, uint64_t seed) {
@@ -716,17 +711,21 @@ int lbm_checkpoint_diagnostics(const lbm_config* cfg, const void* dev_slot, void
   int ndev = 0;
   if (hipGetDeviceCount(&ndev) != hipSuccess || ndev < 1)
     return fail(LBM_ENODEV, "no GPU visible to the HIP runtime");
-  // scratch of the diagnostics kernels, as a handle's workspace holds it:
-  // span sums of chi, per-block partials, one result slot
+  // scratch of the diagnostics kernels, as a handle's workspace holds it: span
+  // sums of chi, partial sums, one result slot. The grids taken are those of
+  // which one slot per 256 columns and z fits beside the span sums in 2^22
+  // doubles; the array holds the larger partial sums of all of them.
   const Layout L = layout_of(cfg, &p);
+  const size_t limit = (size_t)1 << 22;
   const size_t n_chibar = align256((size_t)cfg->nx * cfg->nz * sizeof(double)) / sizeof(double);
-  const size_t n_part = align256((size_t)L.diag_blocks * lbm::kDiagSlots * sizeof(double)) / sizeof(double);
-  const size_t need = n_chibar + n_part + 32;
-  if (need > lbm::kStaticScratchDoubles)
+  const size_t n_256 = (size_t)((cfg->nx + block_x(cfg->nx) - 1) / block_x(cfg->nx)) * cfg->nz;
+  const size_t n_cols = align256(n_256 * lbm::kDiagSlots * sizeof(double)) / sizeof(double);
+  const size_t need = n_chibar + n_cols + 32;
+  const size_t n_part = (L.dres - L.partials) / sizeof(double);
+  if (need > limit || n_chibar + n_part + 32 > lbm::kStaticScratchDoubles)
     return fail(LBM_ENOMEM, "the diagnostics of a %d x %d x %d grid need %zu bytes of scratch; the "
                 "allocation-free entry point holds %zu (nx * nz up to about %zu)", cfg->nx, cfg->ny,
-                cfg->nz, need * sizeof(double), lbm::kStaticScratchDoubles * sizeof(double),
-                lbm::kStaticScratchDoubles - n_part - 32);
+                cfg->nz, need * sizeof(double), limit * sizeof(double), limit - n_cols - 32);
   double* sp = nullptr;
   HIPCHECK(lbm::static_scratch(&sp));
   hipStream_t stream = (hipStream_t)hip_stream;
@@ -760,7 +759,6 @@ int lbm_checkpoint_diagnostics(const lbm_config* cfg, const void* dev_slot, void
   t.chibar = sp;
   t.partials = sp + n_chibar;
   t.dres = sp + n_chibar + n_part;
-  t.diag_blocks = L.diag_blocks;
   t.step = hh.step;
   t.x0 = hh.x0;
   t.initialised = true;

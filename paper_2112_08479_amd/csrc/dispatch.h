@@ -48,6 +48,13 @@ LBM_HD void collide_node(CT* fg, CT* ph, const Phys<CT>& p) {
     collide_cumulant27<LS, LES, CT>(fg, ph, p);
 }
 
+template <typename T>
+LBM_HD double to_d(T v);
+template <>
+LBM_HD double to_d<double>(double v) { return v; }
+template <>
+LBM_HD double to_d<float>(float v) { return (double)v; }
+
 // Post-collision values are not read again before the next launch, so they
 // may bypass the caches on the way to HBM (plain stores measured 5 % slower).
 template <typename ST>
@@ -63,6 +70,11 @@ __device__ __forceinline__ void store_val(ST* p, ST v) {
 
 static inline Grid grid_of(const lbm_handle* h) {
   return Grid{h->cfg.nx, h->cfg.ny, h->cfg.nz, h->n, xblocks(h->cfg.nx)};
+}
+
+static inline int block_x(const lbm_handle* h) {
+  const int nx = h->cfg.nx;
+  return nx >= kBlock ? kBlock : ((nx + 63) / 64) * 64;
 }
 
 template <typename CT>

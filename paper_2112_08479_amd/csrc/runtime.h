@@ -24,15 +24,14 @@ struct lbm_handle {
   void* buf[2];       // population buffers (post-collision values, pull layout)
   int cur;            // index of the buffer holding the current state
   double* chibar;     // nx * nz span sums of chi (diagnostics)
-  double* partials;   // per-block diagnostic partial sums
+  double* partials;   // diagnostic partial sums (diag_partials doubles)
   double* dres;       // 8 doubles: current diagnostics
   double* d0;         // 8 doubles: diagnostics at initialisation
-  double* scratch;    // n doubles (get/set hooks)
+  double* scratch;    // n doubles (get/set hooks, wall shear)
   int64_t step;
   int per_launch;     // steps that the next launch_step makes: 1 or 2
   bool initialised;
   int x0;             // gate index
-  int diag_blocks;
   // the adjoint run's second stream (default priority) and its events, made
   // on first use for a grid whose recomputation overlaps the reverse sweep
   hipStream_t side;
@@ -51,7 +50,6 @@ template <int MODEL, typename ST>
 constexpr int nodes_per_thread() {
   return MODEL == 2 ? 1 : (sizeof(ST) == 2 ? 1 : kNodesPerThread);
 }
-constexpr int kDiagSlots = 8;  // partial sums per diagnostic block
 
 // step.cpp
 // one step src -> dst; fw (the adjoint's forward pass, FP32 / FP64 storage):
@@ -88,20 +86,39 @@ hipError_t launch_step_16<1>(lbm_handle*, const void*, void*, hipStream_t);
 template <>
 hipError_t launch_step_16<2>(lbm_handle*, const void*, void*, hipStream_t);
 
-// kernels.hip
+// init.hip; both also take the initial diagnostics into h->d0
 hipError_t launch_init_lock(lbm_handle* h, double lock_fraction, double amp, uint64_t seed);
 hipError_t launch_init_field(lbm_handle* h, const double* chi0);
+// observe.hip
 hipError_t launch_moments(lbm_handle* h, int dtype, void* rho, void* ux, void* uy, void* uz,
                           void* chi);
 hipError_t launch_wall_shear(lbm_handle* h, int dtype, void* tau, void* tau_bar);
 hipError_t launch_diag(lbm_handle* h, double* out);
+// the second half of launch_diag: the column pass's partial sums and span means
+// (h->partials, h->chibar) into out
+hipError_t launch_diag_reduce(lbm_handle* h, double* out);
+// One block reads small concentration fields for their depth maxima faster than
+// a second launch takes (128 x 16: about 6 us either way); of large ones it
+// makes a serial chain (1024 x 128: 21 us, 2048 x 256: 87 us), so those are
+// reduced by x-block first. Shallow grids have no chain to cut.
+inline bool diag_depth_first(int nx, int nz) { return nz >= 16 && (int64_t)nx * nz >= 16384; }
+// doubles of h->partials: one slot per x-block and z, then, for the depth pass,
+// one per x-block and the columns' maxima
+constexpr int kDiagSlots = 8;
+inline size_t diag_partials(int nx, int nxb, int nz) {
+  return (size_t)nxb * nz * kDiagSlots + (diag_depth_first(nx, nz) ? (size_t)nxb * kDiagSlots + nx : 0);
+}
+// kernels.hip
 hipError_t launch_get_pop(lbm_handle* h, int q, double* dst);
 hipError_t launch_set_pop(lbm_handle* h, int q, const double* src);
 hipError_t launch_copy_state(lbm_handle* h, const void* src, void* dst);
 hipError_t launch_stream_copy(void* dst, const void* src, size_t bytes, hipStream_t stream);
 // device address, on the current device, of the static scratch array of the
-// allocation-free diagnostics (kStaticScratchDoubles doubles)
-constexpr size_t kStaticScratchDoubles = (size_t)1 << 22;
+// allocation-free diagnostics (kStaticScratchDoubles doubles: the grids that
+// the entry point takes, whose span means and 8 doubles per 256 columns fit
+// 2^22, need up to 1.17 of that with the 8 doubles per 64 columns and the
+// columns' maxima that the kernels keep)
+constexpr size_t kStaticScratchDoubles = ((size_t)1 << 22) + ((size_t)1 << 20);
 hipError_t static_scratch(double** ptr);
 
 // adjoint.hip
