@@ -168,14 +168,17 @@ int require_ready(lbm_handle* h) {
   return LBM_OK;
 }
 
-// Whether steps go two at a time. 16-bit storage keeps single steps: its
-// kernels are bound by the vector units, and the ring of the two-step tile would
-// be computed on top (FP16 1024 x 64 x 128: 209 us single, 249 paired); so does
+// Whether steps go two at a time. Single steps stay with 16-bit storage, whose
+// kernels are bound by the vector units, so that the ring of the two-step tile
+// would only add to them (FP16 1024 x 64 x 128: 209 us single, 249 paired), with
 // the 54-population model in FP64, whose nodes in flight do not fit the
-// registers.
+// registers, and with the BGK model in FP32: its span velocity carries the
+// storage's rounding at the 1e-5 level, and runs keep the values they had.
 bool two_steps(const lbm_handle* h) {
   const lbm_config& c = h->cfg;
-  if (c.storage != LBM_F32 && (c.storage != LBM_F64 || c.model == LBM_CUMULANT27_FCM27)) return false;
+  const bool f32 = c.storage == LBM_F32 && c.model != LBM_BGK19_SMAG_Q6;
+  const bool f64 = c.storage == LBM_F64 && c.model != LBM_CUMULANT27_FCM27;
+  if (!f32 && !f64) return false;
   const lbm::Grid g{c.nx, c.ny, c.nz, h->n, lbm::xblocks(c.nx)};
   return lbm::two_step_pays(g, h->qt, (int)h->esize, h->cu_count);
 }
@@ -492,6 +495,7 @@ int lbm_create(const lbm_config* cfg, void* dev_workspace, size_t bytes, void* h
   h->d0 = (double*)(h->ws + L.d0);
   h->scratch = (double*)(h->ws + L.scratch);
   h->step = 0;
+  h->paired = two_steps(h);
   h->per_launch = 1;
   h->initialised = false;
   h->x0 = (int)floor(0.125 * cfg->nx);
@@ -556,9 +560,8 @@ int lbm_step(lbm_handle* h, int64_t n) {
   if (n == 0) return LBM_OK;
   rc = set_device(h);
   if (rc) return rc;
-  const bool pairs = two_steps(h);
   for (int64_t i = 0; i < n;) {
-    h->per_launch = pairs && n - i >= 2 ? 2 : 1;
+    h->per_launch = h->paired && n - i >= 2 ? 2 : 1;
     HIPCHECK(lbm::launch_step(h, h->buf[h->cur], h->buf[h->cur ^ 1]));
     h->cur ^= 1;
     h->step += h->per_launch;

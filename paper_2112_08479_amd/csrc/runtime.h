@@ -29,7 +29,8 @@ struct lbm_handle {
   double* d0;         // 8 doubles: diagnostics at initialisation
   double* scratch;    // n doubles (get/set hooks, wall shear)
   int64_t step;
-  int per_launch;     // steps that the next launch_step makes: 1 or 2
+  bool paired;        // the grid takes steps two at a time
+  int per_launch;     // steps that the next launch makes where it is: 1 or 2
   bool initialised;
   int x0;             // gate index
   // the adjoint run's second stream (default priority) and its events, made
@@ -55,16 +56,17 @@ constexpr int nodes_per_thread() {
 // one step src -> dst; fw (the adjoint's forward pass, FP32 / FP64 storage):
 // also the wall-layer sums of F_w of the gathered state into
 // fw[2 fw_blocks], as launch_fw_layers writes them. st: the stream to launch
-// on (null: the handle's). With h->per_launch = 2 and no fw the launch makes two
-// steps, with the bits of two single ones.
+// on (null: the handle's). With h->paired and no fw the launch makes
+// h->per_launch steps; pairs and single steps of such a handle round alike.
 hipError_t launch_step(lbm_handle* h, const void* src, void* dst, double* fw = nullptr,
                        hipStream_t st = nullptr);
 hipError_t launch_step_fw(lbm_handle* h, const void* src, void* dst, double* fw, hipStream_t st);
-// by model: step_m*.hip, step16_m*.hip
+// by model: step_m*.hip, step16_m*.hip, pair_m*.hip
 template <int MODEL>
 hipError_t launch_step_real(lbm_handle* h, const void* src, void* dst, hipStream_t st);
+// h->per_launch steps of a handle with h->paired
 template <int MODEL>
-hipError_t launch_step2_real(lbm_handle* h, const void* src, void* dst, hipStream_t st);
+hipError_t launch_paired(lbm_handle* h, const void* src, void* dst, hipStream_t st);
 template <int MODEL>
 hipError_t launch_step_16(lbm_handle* h, const void* src, void* dst, hipStream_t st);
 template <>
@@ -74,11 +76,11 @@ hipError_t launch_step_real<1>(lbm_handle*, const void*, void*, hipStream_t);
 template <>
 hipError_t launch_step_real<2>(lbm_handle*, const void*, void*, hipStream_t);
 template <>
-hipError_t launch_step2_real<0>(lbm_handle*, const void*, void*, hipStream_t);
+hipError_t launch_paired<0>(lbm_handle*, const void*, void*, hipStream_t);
 template <>
-hipError_t launch_step2_real<1>(lbm_handle*, const void*, void*, hipStream_t);
+hipError_t launch_paired<1>(lbm_handle*, const void*, void*, hipStream_t);
 template <>
-hipError_t launch_step2_real<2>(lbm_handle*, const void*, void*, hipStream_t);
+hipError_t launch_paired<2>(lbm_handle*, const void*, void*, hipStream_t);
 template <>
 hipError_t launch_step_16<0>(lbm_handle*, const void*, void*, hipStream_t);
 template <>

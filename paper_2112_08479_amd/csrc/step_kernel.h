@@ -74,8 +74,10 @@ __device__ __forceinline__ void step_tile(const ST* __restrict__ src, ST* __rest
   });
 }
 
+// PAIRED: the instance of the translation units of paired steps, which contract
+// multiply-adds in their own way and must not be merged with the others'.
 template <int MODEL, typename ST, typename SS, typename CT, bool LES, int KIND, int NPT,
-          bool FW = false>
+          bool FW = false, bool PAIRED = false>
 __global__ __launch_bounds__(kBlock) void k_step(const ST* __restrict__ src, ST* __restrict__ dst,
                                                  Grid g, Phys<CT> p, int nbx,
                                                  double* __restrict__ fwp) {
@@ -83,7 +85,7 @@ __global__ __launch_bounds__(kBlock) void k_step(const ST* __restrict__ src, ST*
                                                    xcd_row_order(blockIdx.x, gridDim.x, nbx), fwp);
 }
 
-template <int M, typename ST, typename SS, typename CT, int NPT, bool FW>
+template <int M, typename ST, typename SS, typename CT, int NPT, bool FW, bool PAIRED = false>
 static hipError_t launch_step_npt(lbm_handle* h, const Grid& g, const void* src, void* dst,
                                   double* fw, hipStream_t st) {
   const int per_thread_x = (g.nx + NPT - 1) / NPT;  // x-extent in threads if one block
@@ -99,7 +101,7 @@ static hipError_t launch_step_npt(lbm_handle* h, const Grid& g, const void* src,
     if constexpr (FW && KIND == kCumGeneral) {  // not differentiated
       return hipErrorInvalidValue;
     } else {
-      hipLaunchKernelGGL((k_step<M, ST, SS, CT, LES, KIND, NPT, FW>), dim3(blocks), dim3(bx), 0, st, s, d, g, p, nbx, fw);
+      hipLaunchKernelGGL((k_step<M, ST, SS, CT, LES, KIND, NPT, FW, PAIRED>), dim3(blocks), dim3(bx), 0, st, s, d, g, p, nbx, fw);
       return hipGetLastError();
     }
   });

@@ -278,8 +278,9 @@ __global__ __launch_bounds__(64 * (TY + 3),
 }
 
 template <int M, typename T>
-static hipError_t launch_step2_of(lbm_handle* h, const void* src, void* dst, hipStream_t stream) {
+static hipError_t launch_paired_of(lbm_handle* h, const void* src, void* dst, hipStream_t stream) {
   const Grid g = grid_of(h);
+  if (h->per_launch == 1) return launch_step_npt<M, T, T, T, 1, false, true>(h, g, src, dst, nullptr, stream);
   return with_collision<M>(h, [&](auto les, auto kind) {
     constexpr int TY = two_step_rows(sizeof(T));
     TwoStep ts;
