@@ -18,29 +18,9 @@
 #include <algorithm>
 
 #include "adjoint.h"
-#include "collide.h"
-#include "lattice.h"
-#include "runtime.h"
+#include "dispatch.h"
 
 namespace lbm {
-
-template <int MODEL>
-struct AModel;
-template <>
-struct AModel<0> {
-  using LF = Q27;
-  using LS = Q7;
-};
-template <>
-struct AModel<1> {
-  using LF = Q19;
-  using LS = Q6;
-};
-template <>
-struct AModel<2> {
-  using LF = Q27;
-  using LS = Q27;
-};
 
 struct AdjStep {
   double a0, a1;        // F_w seed coefficients at z = 0 and z = 1 (0 when not seeded)
@@ -50,13 +30,22 @@ struct AdjStep {
   double* dchi0;        // non-null: write dJ/dchi0 (the step m = 0)
 };
 
-template <int MODEL, typename ST, typename CT, bool LES, bool PARAM = false>
+template <bool NT, typename T>
+__device__ __forceinline__ void put_lambda(T* p, T v) {
+  if constexpr (NT)
+    __builtin_nontemporal_store(v, p);
+  else
+    *p = v;
+}
+
+// NT: the stores pass the caches.
+template <int MODEL, typename ST, typename CT, bool LES, bool PARAM, bool NT>
 __global__ __launch_bounds__(kBlock) void k_adjoint_step(const ST* __restrict__ state,
                                                          const CT* __restrict__ lam_next,
                                                          CT* __restrict__ lam_out, Grid g,
                                                          Phys<CT> p, AdjStep a, int nbx) {
-  using LF = typename AModel<MODEL>::LF;
-  using LS = typename AModel<MODEL>::LS;
+  using LF = typename ModelT<MODEL>::LF;
+  using LS = typename ModelT<MODEL>::LS;
   constexpr int QT = LF::Q + LS::Q;
   // a row's tiles on one XCD, as in the step kernel: the pulls across tile
   // edges then find the neighbouring tile's lines in the same L2
@@ -140,11 +129,11 @@ __global__ __launch_bounds__(kBlock) void k_adjoint_step(const ST* __restrict__ 
     CT* orow = lam_out + (int64_t)row * g.nxb * (QT * kXB);
     static_for<0, LF::Q>([&](auto qc) {
       constexpr int q = decltype(qc)::value;
-      orow[q * kXB + t.own[0]] = gb[q];
+      put_lambda<NT>(&orow[q * kXB + t.own[0]], gb[q]);
     });
     static_for<0, LS::Q>([&](auto qc) {
       constexpr int q = decltype(qc)::value;
-      orow[(LF::Q + q) * kXB + t.own[0]] = pb[q];
+      put_lambda<NT>(&orow[(LF::Q + q) * kXB + t.own[0]], pb[q]);
     });
     if (a.dchi0) {
       double s = 0.0;
@@ -187,8 +176,8 @@ __global__ __launch_bounds__(kBlock) void k_adjoint_seed(const ST* __restrict__ 
                                                          CT* __restrict__ lam, Grid g, double a0,
                                                          double a1, const double* __restrict__ fs,
                                                          int nbx) {
-  using LF = typename AModel<MODEL>::LF;
-  using LS = typename AModel<MODEL>::LS;
+  using LF = typename ModelT<MODEL>::LF;
+  using LS = typename ModelT<MODEL>::LS;
   const int b = blockIdx.x;
   const int row = b / nbx;
   const int x = (b - row * nbx) * blockDim.x + threadIdx.x;
@@ -276,8 +265,8 @@ __global__ __launch_bounds__(64) void k_fw_layers(const ST* __restrict__ state, 
                                                   double* __restrict__ part) {
   // one wavefront per (x-block, y, z) of the two wall layers z = 0, 1: the
   // block's z is uniform, its sum goes to slot z of the block's pair
-  using LF = typename AModel<MODEL>::LF;
-  constexpr int QT = LF::Q + AModel<MODEL>::LS::Q;
+  using LF = typename ModelT<MODEL>::LF;
+  constexpr int QT = LF::Q + ModelT<MODEL>::LS::Q;
   const int b = blockIdx.x;
   const int xb = b % g.nxb, y = (b / g.nxb) % g.ny, z = b / (g.nxb * g.ny);
   const int x = xb * kXB + (int)threadIdx.x;
@@ -369,12 +358,11 @@ __global__ void k_zero(double* p, int64_t n) {
 }
 
 // ---------------------------------------------------------------- launchers
-static Grid agrid(const lbm_handle* h) {
-  return Grid{h->cfg.nx, h->cfg.ny, h->cfg.nz, h->n, xblocks(h->cfg.nx)};
-}
+// The parametrised kernel's LDS holds a column per thread of a full block, so
+// its blocks stay as full as a row allows.
 static int ablock(const lbm_handle* h) {
-  const int nx = h->cfg.nx;
-  return nx >= kBlock ? kBlock : ((nx + 63) / 64) * 64;
+  if (h->cfg.parametrized) return block_x(h);
+  return tile_threads(h->cfg.nx, (int64_t)h->cfg.ny * h->cfg.nz, 1);
 }
 
 int adjoint_blocks(const lbm_handle* h) {
@@ -384,34 +372,6 @@ int adjoint_blocks(const lbm_handle* h) {
 }
 int fw_blocks(const lbm_handle* h) {
   return xblocks(h->cfg.nx) * h->cfg.ny * std::min(h->cfg.nz, 2);
-}
-
-template <typename CT>
-static Phys<CT> aphys(const lbm_handle* h) {
-  const lbm_params& q = h->prm;
-  const lbm_config& c = h->cfg;
-  Phys<CT> r;
-  r.g = (CT)q.g_prime;
-  r.tau0 = (CT)q.tau0;
-  r.tau_phi0 = (CT)q.tau_phi0;
-  r.c_les = (CT)(18.0 * sqrt(2.0) * (c.smag_paper_form ? c.cs_smag : c.cs_smag * c.cs_smag));
-  r.d0 = (CT)q.d0;
-  r.inv_sct = (CT)(1.0 / c.sc_t);
-  r.inv_cs2phi = (CT)(1.0 / q.cs2_phi);
-  r.omega2 = (CT)c.omega_bulk;
-  r.omega3 = (CT)c.omega3;
-  r.omega4 = (CT)c.omega4;
-  r.omega5 = (CT)c.omega5;
-  r.omega6 = (CT)c.omega6;
-  // parametrised cumulant (as for the forward step)
-  const double h4 = q.tau0 - 0.5;  // 1/omega1 - 1/2
-  r.w_plus = (CT)q.w_plus;
-  r.w_minus = (CT)q.w_minus;
-  r.w_111 = (CT)q.w_111;
-  r.a4 = (CT)(-2.0 / 3.0 * h4 * q.coef_a);
-  r.b4 = (CT)(-1.0 / 3.0 * h4 * q.coef_b);
-  r.lam = c.limiter > 0.0 ? (CT)c.limiter : (CT)INFINITY;
-  return r;
 }
 
 template <class F>
@@ -430,7 +390,7 @@ static hipError_t adj_dispatch(const lbm_handle* h, F&& f) {
 
 hipError_t launch_adjoint_step(lbm_handle* h, const void* state, const void* lam_next,
                                void* lam_out, double a0, double a1, double* gpart, double* dchi0) {
-  const Grid g = agrid(h);
+  const Grid g = grid_of(h);
   const int bx = ablock(h);
   const int nbx = (g.nx + bx - 1) / bx;
   const unsigned blocks = (unsigned)((int64_t)nbx * g.ny * g.nz);
@@ -446,26 +406,36 @@ hipError_t launch_adjoint_step(lbm_handle* h, const void* state, const void* lam
     constexpr int M = decltype(mc)::value;
     using CT = decltype(ct);
     using ST = CT;
-    const Phys<CT> p = aphys<CT>(h);
-    if (M != 1 && h->cfg.parametrized)  // never with the LES
-      hipLaunchKernelGGL((k_adjoint_step<M, ST, CT, false, true>), dim3(blocks), dim3(bx), 0, h->stream,
-                         static_cast<const ST*>(state), static_cast<const CT*>(lam_next),
-                         static_cast<CT*>(lam_out), g, p, a, nbx);
-    else if (les)
-      hipLaunchKernelGGL((k_adjoint_step<M, ST, CT, true>), dim3(blocks), dim3(bx), 0, h->stream,
-                         static_cast<const ST*>(state), static_cast<const CT*>(lam_next),
-                         static_cast<CT*>(lam_out), g, p, a, nbx);
+    const Phys<CT> p = phys_of<CT>(h);
+    auto launch = [&](auto les_c, auto param_c, auto nt_c) {
+      hipLaunchKernelGGL((k_adjoint_step<M, ST, CT, decltype(les_c)::value, decltype(param_c)::value, decltype(nt_c)::value>),
+                         dim3(blocks), dim3(bx), 0, h->stream, static_cast<const ST*>(state),
+                         static_cast<const CT*>(lam_next), static_cast<CT*>(lam_out), g, p, a, nbx);
+    };
+    using Y = std::true_type;
+    using N = std::false_type;
+    // lambda is read back by the next launch, beside a state of the same size:
+    // plain stores while the last-level cache holds them (400 x 24 x 50 FP32, 73
+    // MB a buffer: 100 steps in 8.4 ms against 8.55 past the caches), past the
+    // caches beyond (146 MB 10.1 against 9.7, 1141 MB 52.3 against 50.2)
+    const bool nt = h->state_bytes > ((size_t)120 << 20);
+    if constexpr (M != 1) {
+      if (h->cfg.parametrized) {  // never with the LES
+        nt ? launch(N{}, Y{}, Y{}) : launch(N{}, Y{}, N{});
+        return hipGetLastError();
+      }
+    }
+    if (les)
+      nt ? launch(Y{}, N{}, Y{}) : launch(Y{}, N{}, N{});
     else
-      hipLaunchKernelGGL((k_adjoint_step<M, ST, CT, false>), dim3(blocks), dim3(bx), 0, h->stream,
-                         static_cast<const ST*>(state), static_cast<const CT*>(lam_next),
-                         static_cast<CT*>(lam_out), g, p, a, nbx);
+      nt ? launch(N{}, N{}, Y{}) : launch(N{}, N{}, N{});
     return hipGetLastError();
   });
 }
 
 hipError_t launch_adjoint_seed(lbm_handle* h, const void* state, void* lam, double a0, double a1,
                                const double* fs) {
-  const Grid g = agrid(h);
+  const Grid g = grid_of(h);
   const int bx = ablock(h);
   const int nbx = (g.nx + bx - 1) / bx;
   const unsigned blocks = (unsigned)((int64_t)nbx * g.ny * g.nz);
@@ -479,13 +449,13 @@ hipError_t launch_adjoint_seed(lbm_handle* h, const void* state, void* lam, doub
 }
 
 hipError_t launch_front_seed(lbm_handle* h, double w_front, double* out) {
-  hipLaunchKernelGGL(k_front_seed, dim3(1), dim3(1024), 0, h->stream, h->chibar, agrid(h), w_front,
+  hipLaunchKernelGGL(k_front_seed, dim3(1), dim3(1024), 0, h->stream, h->chibar, grid_of(h), w_front,
                      out);
   return hipGetLastError();
 }
 
 hipError_t launch_fw_layers(lbm_handle* h, const void* state, double* part) {
-  const Grid g = agrid(h);
+  const Grid g = grid_of(h);
   const int nb = fw_blocks(h);
   return adj_dispatch(h, [&](auto mc, auto ct) {
     constexpr int M = decltype(mc)::value;

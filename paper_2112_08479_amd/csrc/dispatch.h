@@ -56,10 +56,12 @@ template <>
 LBM_HD double to_d<float>(float v) { return (double)v; }
 
 // Post-collision values are not read again before the next launch, so they
-// may bypass the caches on the way to HBM (plain stores measured 5 % slower).
-template <typename ST>
+// may bypass the caches on the way to HBM (NT; see stores_past_caches).
+template <bool NT = true, typename ST>
 __device__ __forceinline__ void store_val(ST* p, ST v) {
-  if constexpr (std::is_same<ST, double>::value || std::is_same<ST, float>::value) {
+  if constexpr (!NT) {
+    *p = v;
+  } else if constexpr (std::is_same<ST, double>::value || std::is_same<ST, float>::value) {
     __builtin_nontemporal_store(v, p);
   } else {
     uint16_t bits;

@@ -194,6 +194,31 @@ LBM_HD const ST* pull_ptr(const ST* __restrict__ src, const Grid& g, int base, i
 template <int I, int N, class F>
 LBM_HD void static_for(F&& f);
 
+// Threads of a row tile's block, npt nodes per thread. A row takes whole waves
+// of 64 npt nodes; a block of 4 or 2 of them where that divides the row, else
+// of one, so that no wave of a block is past the row's end (320 x 20 x 40 FP32
+// step: 5 waves a row, 19.2 us in blocks of 256, 15.8 in blocks of 64). Grids
+// of few waves go out one by one (128 x 8 x 16 FP64: 5.3 us against 5.6 in
+// pairs).
+LBM_HD int tile_threads(int nx, int64_t rows, int npt) {
+  const int w = (nx + kXB * npt - 1) / (kXB * npt);
+  if (w * rows <= 512) return 64;
+  return w % 4 == 0 ? 256 : (w % 2 == 0 ? 128 : 64);
+}
+
+// Whether a step's results leave past the caches. Buffers that the 256 MB
+// last-level cache holds beside their source are read back from it by the next
+// step, and plain stores put them there; buffers of a few MB, and those beyond
+// the cache, are faster out of the way. Measured, us per step non-temporal /
+// plain: 9 MB 6.4 / 7.3, 17.8 MB 8.8 / 9.9, 28 MB 13.3 / 11.0, 35 MB 15.8 / 11.9,
+// 73 MB 26.5 / 20.0, 105 MB 38.4 / 27.6, 143 MB 51.5 / 46.7, 285 MB 104 / 110,
+// 481 MB 167 / 174; 16-bit elements 71 MB 30.2 / 27.8, 113 MB 46.0 / 43.9, 139 MB
+// 53.2 / 56.2.
+inline bool stores_past_caches(size_t state_bytes, size_t element_bytes) {
+  return state_bytes < ((size_t)23 << 20) ||
+         state_bytes > ((size_t)(element_bytes == 2 ? 120 : 190) << 20);
+}
+
 // Block order of the row-tiled kernels. Consecutive block ids are dealt
 // round-robin to the 8 XCDs, each with its own L2, and the tiles of one row
 // share a cache line at each tile edge (the x-shifted pulls read one element

@@ -61,11 +61,11 @@ constexpr int nodes_per_thread() {
 hipError_t launch_step(lbm_handle* h, const void* src, void* dst, double* fw = nullptr,
                        hipStream_t st = nullptr);
 hipError_t launch_step_fw(lbm_handle* h, const void* src, void* dst, double* fw, hipStream_t st);
-// by model: step_m*.hip, step16_m*.hip, pair_m*.hip
+// by model: step_m*.hip, step16_m*.hip, pair_m*.hip (models and types that take pairs)
 template <int MODEL>
 hipError_t launch_step_real(lbm_handle* h, const void* src, void* dst, hipStream_t st);
 // h->per_launch steps of a handle with h->paired
-template <int MODEL>
+template <int MODEL, typename T>
 hipError_t launch_paired(lbm_handle* h, const void* src, void* dst, hipStream_t st);
 template <int MODEL>
 hipError_t launch_step_16(lbm_handle* h, const void* src, void* dst, hipStream_t st);
@@ -76,11 +76,13 @@ hipError_t launch_step_real<1>(lbm_handle*, const void*, void*, hipStream_t);
 template <>
 hipError_t launch_step_real<2>(lbm_handle*, const void*, void*, hipStream_t);
 template <>
-hipError_t launch_paired<0>(lbm_handle*, const void*, void*, hipStream_t);
+hipError_t launch_paired<0, float>(lbm_handle*, const void*, void*, hipStream_t);
 template <>
-hipError_t launch_paired<1>(lbm_handle*, const void*, void*, hipStream_t);
+hipError_t launch_paired<0, double>(lbm_handle*, const void*, void*, hipStream_t);
 template <>
-hipError_t launch_paired<2>(lbm_handle*, const void*, void*, hipStream_t);
+hipError_t launch_paired<1, double>(lbm_handle*, const void*, void*, hipStream_t);
+template <>
+hipError_t launch_paired<2, float>(lbm_handle*, const void*, void*, hipStream_t);
 template <>
 hipError_t launch_step_16<0>(lbm_handle*, const void*, void*, hipStream_t);
 template <>

@@ -10,10 +10,12 @@ hipError_t launch_step(lbm_handle* h, const void* src, void* dst, double* fw, hi
   if (!st) st = h->stream;
   if (fw) return launch_step_fw(h, src, dst, fw, st);
   if (h->paired) {
+    const bool f64 = h->cfg.storage == LBM_F64;
     switch (h->cfg.model) {
-      case LBM_CUMULANT27_Q7: return launch_paired<0>(h, src, dst, st);
-      case LBM_BGK19_SMAG_Q6: return launch_paired<1>(h, src, dst, st);
-      case LBM_CUMULANT27_FCM27: return launch_paired<2>(h, src, dst, st);
+      case LBM_CUMULANT27_Q7:
+        return f64 ? launch_paired<0, double>(h, src, dst, st) : launch_paired<0, float>(h, src, dst, st);
+      case LBM_BGK19_SMAG_Q6: return launch_paired<1, double>(h, src, dst, st);
+      case LBM_CUMULANT27_FCM27: return launch_paired<2, float>(h, src, dst, st);
     }
     return hipErrorInvalidValue;
   }

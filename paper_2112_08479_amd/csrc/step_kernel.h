@@ -14,8 +14,9 @@ namespace lbm {
 // the state they gather, as the separate wall-layer kernel does: per x-block
 // the wave sum of u_x = j_x / rho (FP64, populations in order) into
 // fwp[2 b + z], with b = xb + nxb (y + ny z), and 0 into the other slot.
-template <int MODEL, typename ST, typename SS, typename CT, bool LES, int KIND, int NPT,
-          bool FW = false>
+// NT: the stores pass the caches.
+template <int MODEL, typename ST, typename SS, typename CT, bool LES, int KIND, int NPT, bool FW,
+          bool NT>
 __device__ __forceinline__ void step_tile(const ST* __restrict__ src, ST* __restrict__ dst,
                                           const Grid& g, const Phys<CT>& p, int nbx, int b,
                                           double* __restrict__ fwp) {
@@ -66,9 +67,9 @@ __device__ __forceinline__ void step_tile(const ST* __restrict__ src, ST* __rest
     for (int k = 0; k < NPT; ++k) {
       if ((k == 0 && !FW) || t.x[k] < g.nx) {
         if constexpr (a < LF::Q)
-          store_val(&pa[t.own[k]], Conv<ST, CT>::store(fg[k][a]));
+          store_val<NT>(&pa[t.own[k]], Conv<ST, CT>::store(fg[k][a]));
         else
-          store_val(&reinterpret_cast<SS*>(pa)[t.own[k]], Conv<SS, CT>::store(ph[k][a - LF::Q]));
+          store_val<NT>(&reinterpret_cast<SS*>(pa)[t.own[k]], Conv<SS, CT>::store(ph[k][a - LF::Q]));
       }
     }
   });
@@ -77,19 +78,18 @@ __device__ __forceinline__ void step_tile(const ST* __restrict__ src, ST* __rest
 // PAIRED: the instance of the translation units of paired steps, which contract
 // multiply-adds in their own way and must not be merged with the others'.
 template <int MODEL, typename ST, typename SS, typename CT, bool LES, int KIND, int NPT,
-          bool FW = false, bool PAIRED = false>
+          bool FW, bool PAIRED, bool NT>
 __global__ __launch_bounds__(kBlock) void k_step(const ST* __restrict__ src, ST* __restrict__ dst,
                                                  Grid g, Phys<CT> p, int nbx,
                                                  double* __restrict__ fwp) {
-  step_tile<MODEL, ST, SS, CT, LES, KIND, NPT, FW>(src, dst, g, p, nbx,
+  step_tile<MODEL, ST, SS, CT, LES, KIND, NPT, FW, NT>(src, dst, g, p, nbx,
                                                    xcd_row_order(blockIdx.x, gridDim.x, nbx), fwp);
 }
 
 template <int M, typename ST, typename SS, typename CT, int NPT, bool FW, bool PAIRED = false>
 static hipError_t launch_step_npt(lbm_handle* h, const Grid& g, const void* src, void* dst,
                                   double* fw, hipStream_t st) {
-  const int per_thread_x = (g.nx + NPT - 1) / NPT;  // x-extent in threads if one block
-  const int bx = per_thread_x >= kBlock ? kBlock : ((per_thread_x + 63) / 64) * 64;
+  const int bx = tile_threads(g.nx, (int64_t)g.ny * g.nz, NPT);
   const int nbx = (g.nx + bx * NPT - 1) / (bx * NPT);
   const unsigned blocks = (unsigned)((int64_t)nbx * g.ny * g.nz);
   const Phys<CT> p = phys_of<CT>(h);
@@ -101,7 +101,10 @@ static hipError_t launch_step_npt(lbm_handle* h, const Grid& g, const void* src,
     if constexpr (FW && KIND == kCumGeneral) {  // not differentiated
       return hipErrorInvalidValue;
     } else {
-      hipLaunchKernelGGL((k_step<M, ST, SS, CT, LES, KIND, NPT, FW, PAIRED>), dim3(blocks), dim3(bx), 0, st, s, d, g, p, nbx, fw);
+      if (stores_past_caches(h->state_bytes, h->esize))
+        hipLaunchKernelGGL((k_step<M, ST, SS, CT, LES, KIND, NPT, FW, PAIRED, true>), dim3(blocks), dim3(bx), 0, st, s, d, g, p, nbx, fw);
+      else
+        hipLaunchKernelGGL((k_step<M, ST, SS, CT, LES, KIND, NPT, FW, PAIRED, false>), dim3(blocks), dim3(bx), 0, st, s, d, g, p, nbx, fw);
       return hipGetLastError();
     }
   });

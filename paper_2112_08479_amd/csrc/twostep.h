@@ -83,14 +83,15 @@ inline int64_t two_step_plan(const Grid& g, int ty, int cus, TwoStep& s) {
 }
 
 // Two steps at a time halve the traffic but need a grid whose tiles keep every
-// CU busy: `work` is the tile planes per CU if nothing were lost to ragged
-// tiles, chunk ends and a part-filled last round, `spent` those that the plan
-// takes. Measured per step, single against paired (MI355X, model 0 FP32):
-// 256 x 16 x 32 (work 1.0, spent 4) 9.0 / 11.7 us, 400 x 24 x 50 (3.7, 8)
-// 29.6 / 26.3, 512 x 32 x 64 (8, 11) 54.9 / 41.6, 800 x 50 x 100 (30.5, 46)
-// 199 / 182, 1024 x 64 x 128 (64, 67) 391 / 286; FP64 256 x 16 x 32 (1.6, 5)
-// 15.9 / 16.1, 400 x 24 x 50 (5.9, 11) 52.8 / 48.1. A pull reaches over three planes with 32-bit
-// offsets, which bounds their size.
+// CU busy, and one that the caches do not hold anyway: `work` is the tile planes
+// per CU if nothing were lost to ragged tiles, chunk ends and a part-filled last
+// round, `spent` those that the plan takes. Measured per step, single against
+// paired (MI355X, cumulant + D3Q7): FP32 256 x 16 x 32 (work 1.0, spent 4) 8.9 /
+// 11.7 us, 400 x 24 x 50 (3.7, 8) 21.8 / 24.4, 448 x 28 x 56 (5.4, 10) 29.5 / 29.7,
+// 512 x 32 x 64 (8, 11) 46.7 / 40.1, 800 x 50 x 100 (30.5, 46) 186 / 179, 1024 x
+// 64 x 128 (64, 67) 391 / 283; FP64 320 x 20 x 40 (3.1, 7) 21.7 / 24.8, 400 x 24 x
+// 50 (5.9, 11) 47.9 / 41.6, 512 x 32 x 64 (12.8, 17) 104 / 80. A pull reaches over
+// three planes with 32-bit offsets, which bounds their size.
 inline bool two_step_pays(const Grid& g, int qt, int bytes, int cus) {
   const int64_t plane = (int64_t)g.ny * g.nxb * kXB * qt * bytes;
   if (3 * plane >= ((int64_t)1 << 31)) return false;
@@ -98,7 +99,7 @@ inline bool two_step_pays(const Grid& g, int qt, int bytes, int cus) {
   TwoStep s;
   const double spent = (double)two_step_plan(g, ty, cus, s);
   const double work = (double)g.n / ((double)kXB * ty * cus);
-  return work >= 1.7 && spent <= 1.5 * work + 2.9;
+  return spent <= 1.6 * work + 2.0;
 }
 
 struct Tile {

@@ -59,10 +59,9 @@ __device__ __forceinline__ T load_at(Rsrc r, uint32_t lane, int scalar) {
 }
 // a lane offset beyond every plane (three planes are below 2 GiB)
 constexpr uint32_t kDropped = 0x80000000u;
-// non-temporal, as store_val
-template <typename T>
+template <bool NT, typename T>
 __device__ __forceinline__ void store_at(Rsrc r, uint32_t lane, int scalar, T v) {
-  constexpr int kNt = 2;
+  constexpr int kNt = NT ? 2 : 0;
   if constexpr (sizeof(T) == 8) {
     typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
     __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, lane, scalar, kNt);
@@ -150,7 +149,7 @@ __device__ __forceinline__ void pull_plane(const Planes& s, const Grid& g, int z
   }
 }
 
-template <int MODEL, typename ST, typename SS, typename CT, bool LES, int KIND, int TY>
+template <int MODEL, typename ST, typename SS, typename CT, bool LES, int KIND, int TY, bool NT>
 __global__ __launch_bounds__(64 * (TY + 3),
                              tile_waves<ST>()) void k_step2(const ST* __restrict__ src,
                                                          ST* __restrict__ dst, Grid g, Phys<CT> p,
@@ -257,9 +256,9 @@ __global__ __launch_bounds__(64 * (TY + 3),
         constexpr int a = decltype(ac)::value;
         constexpr int seg = a * kXB * (int)sizeof(ST);
         if constexpr (P::flow(a))
-          store_at(rd, to, seg, Conv<ST, CT>::store(f2[a]));
+          store_at<NT>(rd, to, seg, Conv<ST, CT>::store(f2[a]));
         else
-          store_at(rd, to, seg, Conv<SS, CT>::store(p2[a - LF::Q]));
+          store_at<NT>(rd, to, seg, Conv<SS, CT>::store(p2[a - LF::Q]));
       });
     };
     // Stores by every wave, those of lanes without a second-step node out of
@@ -285,9 +284,15 @@ static hipError_t launch_paired_of(lbm_handle* h, const void* src, void* dst, hi
     constexpr int TY = two_step_rows(sizeof(T));
     TwoStep ts;
     two_step_plan(g, TY, h->cu_count, ts);
-    hipLaunchKernelGGL((k_step2<M, T, T, T, decltype(les)::value, decltype(kind)::value, TY>),
-                       dim3(ts.nblocks), dim3(64 * (TY + 3)), 0, stream, static_cast<const T*>(src),
-                       static_cast<T*>(dst), g, phys_of<T>(h), ts);
+    auto launch = [&](auto nt) {
+      hipLaunchKernelGGL((k_step2<M, T, T, T, decltype(les)::value, decltype(kind)::value, TY, decltype(nt)::value>),
+                         dim3(ts.nblocks), dim3(64 * (TY + 3)), 0, stream, static_cast<const T*>(src),
+                         static_cast<T*>(dst), g, phys_of<T>(h), ts);
+    };
+    if (stores_past_caches(h->state_bytes, h->esize))
+      launch(std::true_type{});
+    else
+      launch(std::false_type{});
     return hipGetLastError();
   });
 }
