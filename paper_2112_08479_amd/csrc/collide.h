@@ -121,6 +121,110 @@ LBM_HD void inverse_chimera(const CT* m, CT ux, CT uy, CT uz, CT* g) {
   });
 }
 
+// ---- the lean forms: the same quantities in fewer operations, for the kernels
+// that the vector units bound (the paired steps, whose two collisions per node
+// take 64 % of the time). The moments come from sums over x shared by all of
+// them (67 additions for 190), the transform back shares its two halves (8
+// operations a triple for 10) and leaves out the odd moments that vanish, the
+// scalar's equilibria come in pairs. Their rounding errors are of the same size,
+// not the same values.
+
+// inverse of fwd1d; A = K + o0, uu = u^2, u2 = 2 u
+template <typename CT>
+LBM_HD void inv1d_lean(CT o0, CT o1, CT o2, CT u, CT uu, CT u2, CT A, CT& tm, CT& t0, CT& tp) {
+  const CT e = o2 + u2 * o1 + uu * A;
+  const CT d = o1 + u * A;
+  const CT h = CT(0.5) * e;
+  t0 = o0 - e;
+  tp = h + CT(0.5) * d;
+  tm = h - CT(0.5) * d;
+}
+
+// EVEN: the moments of odd order are all zero
+template <bool EVEN, typename CT>
+LBM_HD void inverse_chimera_lean(const CT* m, CT ux, CT uy, CT uz, CT* g) {
+  CT A[27], B[27];
+  const CT xx = ux * ux, yy = uy * uy, zz = uz * uz;
+  const CT x2 = ux + ux, y2 = uy + uy, z2 = uz + uz;
+  const CT xp = ux + CT(0.5), xm = ux - CT(0.5);
+  static_for<0, 9>([&](auto ic) {  // x: groups (b, c)
+    constexpr int i = decltype(ic)::value, b = i / 3, c = i % 3;
+    constexpr double K = k1d(b) * k1d(c);
+    CT &tm = B[i], &t0 = B[9 + i], &tp = B[18 + i];
+    if constexpr (EVEN && (b + c) % 2 == 1) {  // only the first order in x
+      t0 = -(x2 * m[9 + i]);
+      tp = xp * m[9 + i];
+      tm = xm * m[9 + i];
+    } else if constexpr (EVEN) {
+      const CT a = K == 0 ? m[i] : CT(K) + m[i];
+      const CT e = m[18 + i] + xx * a;
+      const CT d = ux * a;
+      const CT h = CT(0.5) * e;
+      t0 = m[i] - e;
+      tp = h + CT(0.5) * d;
+      tm = h - CT(0.5) * d;
+    } else {
+      inv1d_lean<CT>(m[i], m[9 + i], m[18 + i], ux, xx, x2, K == 0 ? m[i] : CT(K) + m[i], tm, t0, tp);
+    }
+  });
+  static_for<0, 9>([&](auto ic) {  // y: groups (cx, c)
+    constexpr int i = decltype(ic)::value, o = i / 3 * 9 + i % 3;
+    constexpr double K = w1d(i / 3) * k1d(i % 3);
+    inv1d_lean<CT>(B[o], B[o + 3], B[o + 6], uy, yy, y2, K == 0 ? B[o] : CT(K) + B[o], A[o], A[o + 3],
+                   A[o + 6]);
+  });
+  static_for<0, 9>([&](auto ic) {  // z: groups (cx, cy)
+    constexpr int i = decltype(ic)::value, cxi = i / 3, cyi = i % 3, o = 3 * i;
+    constexpr double K = w1d(cxi) * w1d(cyi);
+    inv1d_lean<CT>(A[o], A[o + 1], A[o + 2], uz, zz, z2, CT(K) + A[o], g[idx27(cxi - 1, cyi - 1, -1)],
+                   g[idx27(cxi - 1, cyi - 1, 0)], g[idx27(cxi - 1, cyi - 1, 1)]);
+  });
+}
+
+// Sums over D3Q27 by x-triples: E = f+ + f-, S = E + f0, D = f+ - f- at each
+// (c_y, c_z), indexed c + 1.
+template <typename CT>
+struct Triples {
+  CT E[3][3], S[3][3], D[3][3];
+  LBM_HD explicit Triples(const CT* g) {
+    static_for<0, 9>([&](auto ic) {
+      constexpr int b = decltype(ic)::value / 3, c = decltype(ic)::value % 3;
+      const CT p = g[idx27(1, b - 1, c - 1)], m = g[idx27(-1, b - 1, c - 1)];
+      E[b][c] = p + m;
+      D[b][c] = p - m;
+      S[b][c] = E[b][c] + g[idx27(0, b - 1, c - 1)];
+    });
+  }
+  static LBM_HD CT row(const CT (&t)[3][3], int b) { return t[b][0] + t[b][2] + t[b][1]; }
+  static LBM_HD CT col(const CT (&t)[3][3], int c) { return t[0][c] + t[2][c] + t[1][c]; }
+  // density and momentum
+  LBM_HD void first(CT& n, CT& jx, CT& jy, CT& jz) const {
+    const CT a = row(S, 0), b = row(S, 2);
+    n = (a + b) + row(S, 1);
+    jx = (row(D, 0) + row(D, 2)) + row(D, 1);
+    jy = b - a;
+    jz = col(S, 2) - col(S, 0);
+  }
+  LBM_HD void second(CT& xx, CT& yy, CT& zz, CT& xy, CT& xz, CT& yz) const {
+    xx = (row(E, 0) + row(E, 2)) + row(E, 1);
+    yy = row(S, 0) + row(S, 2);
+    zz = col(S, 0) + col(S, 2);
+    xy = row(D, 2) - row(D, 0);
+    xz = col(D, 2) - col(D, 0);
+    yz = (S[2][2] - S[2][0]) - (S[0][2] - S[0][0]);
+  }
+  // as third_raw_sums: 120, 102, 210, 012, 201, 021, 111
+  LBM_HD void third(CT (&r)[7]) const {
+    r[0] = row(D, 0) + row(D, 2);
+    r[1] = col(D, 0) + col(D, 2);
+    r[2] = row(E, 2) - row(E, 0);
+    r[3] = (S[2][0] + S[2][2]) - (S[0][0] + S[0][2]);
+    r[4] = col(E, 2) - col(E, 0);
+    r[5] = (S[0][2] + S[2][2]) - (S[0][0] + S[2][0]);
+    r[6] = (D[2][2] - D[2][0]) - (D[0][2] - D[0][0]);
+  }
+};
+
 // Smagorinsky total relaxation time from q2 = |Pi_neq|^2 / rho^2:
 // tau_f = (tau0 + sqrt(tau0^2 + 18 sqrt(2) C_s^2 sqrt(Q) / rho)) / 2
 // (Eq. 32-34 in the standard form nu_T = (C_s Delta)^2 |S|, Delta = 1).
@@ -143,7 +247,7 @@ LBM_HD CT tree_sum(const CT* v) {
 
 // Scalar BGK (Eq. 28-29): phi* = phi - (phi - w chi (1 + c.u / cs_phi^2)) / tau_phi,
 // tau_phi = 1/2 + (D0 + nu_T / Sc_T) / cs_phi^2 (Eq. 30, 35), nu_T = (tau_f - tau0)/3.
-template <class LS, bool LES, typename CT>
+template <class LS, bool LES, bool LEAN = false, typename CT>
 LBM_HD void collide_scalar(CT* ph, CT chi, CT ux, CT uy, CT uz, CT tau, const Phys<CT>& p) {
   CT tau_phi = p.tau_phi0;
   if constexpr (LES) {
@@ -151,6 +255,18 @@ LBM_HD void collide_scalar(CT* ph, CT chi, CT ux, CT uy, CT uz, CT tau, const Ph
     tau_phi = CT(0.5) + (p.d0 + nu_t * p.inv_sct) * p.inv_cs2phi;
   }
   const CT wphi = CT(1) / tau_phi;
+  if constexpr (LEAN && LS::Q == 7) {
+    // w chi (1 +- u / cs_phi^2) for each axis; the weights 1/4 and 1/8 are exact
+    const CT a = CT(0.125) * chi, u[3] = {ux, uy, uz};
+    ph[0] = ph[0] - wphi * (ph[0] - CT(0.25) * chi);
+    static_for<0, 3>([&](auto dc) {
+      constexpr int q = 1 + 2 * decltype(dc)::value;
+      const CT s = a * (u[decltype(dc)::value] * p.inv_cs2phi);
+      ph[q] = ph[q] - wphi * (ph[q] - (a + s));
+      ph[q + 1] = ph[q + 1] - wphi * (ph[q + 1] - (a - s));
+    });
+    return;
+  }
   CT neq[LS::Q];
   static_for<0, LS::Q>([&](auto qc) {
     constexpr int q = decltype(qc)::value;
@@ -192,7 +308,7 @@ LBM_HD void collide_scalar(CT* ph, CT chi, CT ux, CT uy, CT uz, CT tau, const Ph
 // where P (central moments e about u) and Q (central moments f about u) are
 //   P(-1) = (1/3 + u^2 - u)/2, P(0) = 2/3 - u^2, P(+1) = (1/3 + u^2 + u)/2,
 //   Q(-1) = u - 1/2,           Q(0) = -2u,       Q(+1) = u + 1/2.
-template <bool LES, typename CT>
+template <bool LES, bool LEAN = false, typename CT>
 LBM_HD void collide_fcm27(CT* ph, CT chi, CT ux, CT uy, CT uz, CT tau, const Phys<CT>& p) {
   CT tau_phi = p.tau_phi0;
   if constexpr (LES) {
@@ -201,12 +317,17 @@ LBM_HD void collide_fcm27(CT* ph, CT chi, CT ux, CT uy, CT uz, CT tau, const Phy
   }
   const CT a1 = CT(1) - CT(1) / tau_phi;
   CT jx = CT(0), jy = CT(0), jz = CT(0);
-  static_for<0, 27>([&](auto qc) {
-    constexpr int q = decltype(qc)::value;
-    if (Q27::cx[q]) jx += CT(Q27::cx[q]) * ph[q];
-    if (Q27::cy[q]) jy += CT(Q27::cy[q]) * ph[q];
-    if (Q27::cz[q]) jz += CT(Q27::cz[q]) * ph[q];
-  });
+  if constexpr (LEAN) {
+    CT n;
+    Triples<CT>(ph).first(n, jx, jy, jz);
+  } else {
+    static_for<0, 27>([&](auto qc) {
+      constexpr int q = decltype(qc)::value;
+      if (Q27::cx[q]) jx += CT(Q27::cx[q]) * ph[q];
+      if (Q27::cy[q]) jy += CT(Q27::cy[q]) * ph[q];
+      if (Q27::cz[q]) jz += CT(Q27::cz[q]) * ph[q];
+    });
+  }
   const CT kx = a1 * (jx - chi * ux), ky = a1 * (jy - chi * uy), kz = a1 * (jz - chi * uz);
   CT P[3][3], Qv[3][3];  // [axis][c + 1]
   const CT uu[3] = {ux, uy, uz};
@@ -238,12 +359,12 @@ LBM_HD void collide_fcm27(CT* ph, CT chi, CT ux, CT uy, CT uz, CT tau, const Phy
 
 // scalar collision of the scalar lattice LS: BGK on D3Q7 / D3Q6, factorized
 // central moments on D3Q27
-template <class LS, bool LES, typename CT>
+template <class LS, bool LES, bool LEAN = false, typename CT>
 LBM_HD void scalar_collision(CT* ph, CT chi, CT ux, CT uy, CT uz, CT tau, const Phys<CT>& p) {
   if constexpr (LS::Q == 27)
-    collide_fcm27<LES, CT>(ph, chi, ux, uy, uz, tau, p);
+    collide_fcm27<LES, LEAN>(ph, chi, ux, uy, uz, tau, p);
   else
-    collide_scalar<LS, LES, CT>(ph, chi, ux, uy, uz, tau, p);
+    collide_scalar<LS, LES, LEAN>(ph, chi, ux, uy, uz, tau, p);
 }
 
 // Flow moments of the deviations: drho, j, and raw second moments Pi^g.
@@ -297,10 +418,16 @@ LBM_HD void relax_second(CT a1, CT omega2, CT& xx, CT& yy, CT& zz, CT& xy, CT& x
 // order is reset to its equilibrium value 0): only the second-order
 // cumulants are needed; they come from the raw second moments. LS: the
 // scalar lattice (D3Q7 BGK or D3Q27 factorized central moments).
-template <class LS, bool LES, typename CT>
+template <class LS, bool LES, bool LEAN = false, typename CT>
 LBM_HD void collide_cumulant27(CT* g, CT* ph, const Phys<CT>& p, CT* tau_out = nullptr) {
   CT drho, jx, jy, jz, pxx, pyy, pzz, pxy, pxz, pyz;
-  flow_moments<Q27>(g, drho, jx, jy, jz, pxx, pyy, pzz, pxy, pxz, pyz);
+  if constexpr (LEAN) {
+    const Triples<CT> t(g);
+    t.first(drho, jx, jy, jz);
+    t.second(pxx, pyy, pzz, pxy, pxz, pyz);
+  } else {
+    flow_moments<Q27>(g, drho, jx, jy, jz, pxx, pyy, pzz, pxy, pxz, pyz);
+  }
   const CT chi = scalar_sum<LS>(ph);
   const CT rho = CT(1) + drho;
   const CT irho = CT(1) / rho;
@@ -346,8 +473,11 @@ LBM_HD void collide_cumulant27(CT* g, CT* ph, const Phys<CT>& p, CT* tau_out = n
                           (third + dzz) * dxy * dxy) +
                  CT(8) * dxy * dxz * dyz) +
           drho * CT(1.0 / 27.0);
-  inverse_chimera<CT>(m, ux, uy, (jz + Fz) * irho, g);
-  scalar_collision<LS, LES>(ph, chi, ux, uy, (jz + CT(0.5) * Fz) * irho, tau, p);
+  if constexpr (LEAN)
+    inverse_chimera_lean<true>(m, ux, uy, (jz + Fz) * irho, g);
+  else
+    inverse_chimera<CT>(m, ux, uy, (jz + Fz) * irho, g);
+  scalar_collision<LS, LES, LEAN>(ph, chi, ux, uy, (jz + CT(0.5) * Fz) * irho, tau, p);
 }
 
 // Third-order limiter of the parametrised cumulant: 1 - (limited rate) for
@@ -414,7 +544,7 @@ struct HighCumulants {
 // D = C - delta/3 (dxx..dyz) and the cumulants of orders 3..6: moments about
 // the post-collision mean from cumulants (zero mean), as deviations from the
 // rest values, then the inverse chimera transform.
-template <typename CT>
+template <bool LEAN = false, typename CT>
 LBM_HD void rebuild_from_cumulants(CT* g, CT drho, CT rho, CT dxx, CT dyy, CT dzz, CT dxy, CT dxz,
                                    CT dyz, const HighCumulants<CT>& c, CT ux, CT uy, CT uz) {
   const CT third = CT(1.0 / 3.0), ninth = CT(1.0 / 9.0);
@@ -458,11 +588,14 @@ LBM_HD void rebuild_from_cumulants(CT* g, CT drho, CT rho, CT dxx, CT dyy, CT dz
       CT(2) * ((third + dxx) * dyz * dyz + (third + dyy) * dxz * dxz + (third + dzz) * dxy * dxy) +
       CT(8) * dxy * dxz * dyz;
   put(26, m222s, 1.0 / 27.0);
-  inverse_chimera<CT>(m, ux, uy, uz, g);
+  if constexpr (LEAN)
+    inverse_chimera_lean<false>(m, ux, uy, uz, g);
+  else
+    inverse_chimera<CT>(m, ux, uy, uz, g);
 }
 
 // ---- cumulant collision with general rates omega3..omega6.
-template <class LS, bool LES, typename CT>
+template <class LS, bool LES, bool LEAN = false, typename CT>
 LBM_HD void collide_cumulant27_general(CT* g, CT* ph, const Phys<CT>& p) {
   CT drho = CT(0), jx = CT(0), jy = CT(0), jz = CT(0);
   static_for<0, 27>([&](auto qc) {
@@ -532,8 +665,8 @@ LBM_HD void collide_cumulant27_general(CT* g, CT* ph, const Phys<CT>& p) {
   c.c211 = a4 * c211, c.c121 = a4 * c121, c.c112 = a4 * c112;
   c.c221 = a5 * c221, c.c212 = a5 * c212, c.c122 = a5 * c122;
   c.c222 = a6 * c222;
-  rebuild_from_cumulants<CT>(g, drho, rho, dxx, dyy, dzz, dxy, dxz, dyz, c, ux, uy, (jz + Fz) * irho);
-  scalar_collision<LS, LES>(ph, chi, ux, uy, (jz + CT(0.5) * Fz) * irho, tau, p);
+  rebuild_from_cumulants<LEAN>(g, drho, rho, dxx, dyy, dzz, dxy, dxz, dyz, c, ux, uy, (jz + Fz) * irho);
+  scalar_collision<LS, LES, LEAN>(ph, chi, ux, uy, (jz + CT(0.5) * Fz) * irho, tau, p);
 }
 
 // ---- the parametrised cumulant of Geier, Pasquali and Schoenherr (2017) that
@@ -549,12 +682,19 @@ LBM_HD void collide_cumulant27_general(CT* g, CT* ph, const Phys<CT>& p) {
 // Only the second- and third-order pre-collision cumulants are needed; they
 // come from raw sums of the deviations (the third-order raw moments of the
 // rest state vanish) instead of the full forward transform.
-template <class LS, typename CT>
+template <class LS, bool LEAN = false, typename CT>
 LBM_HD void collide_cumulant27_param(CT* g, CT* ph, const Phys<CT>& p) {
   CT drho, jx, jy, jz, pxx, pyy, pzz, pxy, pxz, pyz;
-  flow_moments<Q27>(g, drho, jx, jy, jz, pxx, pyy, pzz, pxy, pxz, pyz);
   CT r3[7];
-  third_raw_sums<CT>(g, r3);
+  if constexpr (LEAN) {
+    const Triples<CT> t(g);
+    t.first(drho, jx, jy, jz);
+    t.second(pxx, pyy, pzz, pxy, pxz, pyz);
+    t.third(r3);
+  } else {
+    flow_moments<Q27>(g, drho, jx, jy, jz, pxx, pyy, pzz, pxy, pxz, pyz);
+    third_raw_sums<CT>(g, r3);
+  }
   const CT chi = scalar_sum<LS>(ph);
   const CT rho = CT(1) + drho;
   const CT irho = CT(1) / rho;
@@ -604,8 +744,8 @@ LBM_HD void collide_cumulant27_param(CT* g, CT* ph, const Phys<CT>& p) {
   pair(k201, k021, c.c201, c.c021);
   c.c111 = keep(p.w_111, k111) * k111;
   relax_second(CT(1) - w1, p.omega2, dxx, dyy, dzz, dxy, dxz, dyz);
-  rebuild_from_cumulants<CT>(g, drho, rho, dxx, dyy, dzz, dxy, dxz, dyz, c, ux, uy, (jz + Fz) * irho);
-  scalar_collision<LS, false>(ph, chi, ux, uy, (jz + CT(0.5) * Fz) * irho, p.tau0, p);
+  rebuild_from_cumulants<LEAN>(g, drho, rho, dxx, dyy, dzz, dxy, dxz, dyz, c, ux, uy, (jz + Fz) * irho);
+  scalar_collision<LS, false, LEAN>(ph, chi, ux, uy, (jz + CT(0.5) * Fz) * irho, p.tau0, p);
 }
 
 // ---- D3Q19 BGK with Guo forcing (Eq. 21-26), Smagorinsky (Eq. 32-35),

@@ -35,17 +35,18 @@ struct ModelT<2> {
 // parametrised
 enum { kCumFast = 0, kCumGeneral = 1, kCumParam = 2 };
 
-template <int MODEL, bool LES, int KIND, typename CT>
+// LEAN: the lean forms (cumulant models)
+template <int MODEL, bool LES, int KIND, bool LEAN, typename CT>
 LBM_HD void collide_node(CT* fg, CT* ph, const Phys<CT>& p) {
   using LS = typename ModelT<MODEL>::LS;
   if constexpr (MODEL == 1)
     collide_bgk_q19_q6<LES, CT>(fg, ph, p);
   else if constexpr (KIND == kCumParam)
-    collide_cumulant27_param<LS, CT>(fg, ph, p);
+    collide_cumulant27_param<LS, LEAN>(fg, ph, p);
   else if constexpr (KIND == kCumGeneral)
-    collide_cumulant27_general<LS, LES, CT>(fg, ph, p);
+    collide_cumulant27_general<LS, LES, LEAN>(fg, ph, p);
   else
-    collide_cumulant27<LS, LES, CT>(fg, ph, p);
+    collide_cumulant27<LS, LES, LEAN>(fg, ph, p);
 }
 
 template <typename T>

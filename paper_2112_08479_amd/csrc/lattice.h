@@ -239,6 +239,14 @@ LBM_HD int xcd_row_order(int b, int nblocks, int nbx) {
   return r * nbx + i;
 }
 
+// Block order that gives each XCD a contiguous run of blocks (for kernels that
+// read neighbouring rows through L2).
+LBM_HD int xcd_run_order(int b, int nblocks) {
+  constexpr int kXcd = 8;
+  const int xcd = b % kXcd, q = nblocks / kXcd, r = nblocks % kXcd;
+  return xcd * q + (xcd < r ? xcd : r) + b / kXcd;
+}
+
 // Lane geometry of a tile for the x-blocked layout. Thread t handles nodes
 // x = x0 + t + k blockDim.x (k < NPT); x0 and blockDim.x are multiples of 64,
 // so t % 64 is the node's place in its x-block. Offsets are element offsets

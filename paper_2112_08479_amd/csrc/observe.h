@@ -77,6 +77,9 @@ __device__ void block_reduce(double (&v)[NV], int imax) {
   __syncthreads();
 }
 
+// Bound by reading the state: 1024 x 64 x 128 FP32 233 -> 185 us (6.2 TB/s), bf16
+// 185 -> 130 (4.4), 128 x 8 x 16 FP64 16 -> 9, against one thread per column with
+// 64-bit addresses per population, a square root and three divisions per node.
 // One block per x-block and z; its waves take the span rows in turn. node(x, y,
 // z, sums) gives a node's moments; it is called by every lane of a wave, with x
 // held inside the grid. Writes the span mean of chi, and the block's partial

@@ -14,9 +14,9 @@ namespace lbm {
 // the state they gather, as the separate wall-layer kernel does: per x-block
 // the wave sum of u_x = j_x / rho (FP64, populations in order) into
 // fwp[2 b + z], with b = xb + nxb (y + ny z), and 0 into the other slot.
-// NT: the stores pass the caches.
+// PAIRED: the collision of the paired steps. NT: the stores pass the caches.
 template <int MODEL, typename ST, typename SS, typename CT, bool LES, int KIND, int NPT, bool FW,
-          bool NT>
+          bool PAIRED, bool NT>
 __device__ __forceinline__ void step_tile(const ST* __restrict__ src, ST* __restrict__ dst,
                                           const Grid& g, const Phys<CT>& p, int nbx, int b,
                                           double* __restrict__ fwp) {
@@ -57,7 +57,7 @@ __device__ __forceinline__ void step_tile(const ST* __restrict__ src, ST* __rest
     }
   }
 #pragma unroll
-  for (int k = 0; k < NPT; ++k) collide_node<MODEL, LES, KIND, CT>(fg[k], ph[k], p);
+  for (int k = 0; k < NPT; ++k) collide_node<MODEL, LES, KIND, PAIRED>(fg[k], ph[k], p);
   // block-uniform segment pointers + the lane's own offset, as for the loads
   ST* drow = dst + (int64_t)row * g.nxb * (QT * kXB);
   static_for<0, QT>([&](auto qc) {
@@ -82,7 +82,7 @@ template <int MODEL, typename ST, typename SS, typename CT, bool LES, int KIND, 
 __global__ __launch_bounds__(kBlock) void k_step(const ST* __restrict__ src, ST* __restrict__ dst,
                                                  Grid g, Phys<CT> p, int nbx,
                                                  double* __restrict__ fwp) {
-  step_tile<MODEL, ST, SS, CT, LES, KIND, NPT, FW, NT>(src, dst, g, p, nbx,
+  step_tile<MODEL, ST, SS, CT, LES, KIND, NPT, FW, PAIRED, NT>(src, dst, g, p, nbx,
                                                    xcd_row_order(blockIdx.x, gridDim.x, nbx), fwp);
 }
 
@@ -118,15 +118,15 @@ static bool few_waves(const lbm_handle* h, int npt) {
   return waves < (int64_t)16 * h->cu_count;
 }
 
-template <int M, typename ST, typename SS, typename CT, bool FW = false>
+template <int M, typename ST, typename SS, typename CT, bool FW = false, bool PAIRED = false>
 static hipError_t launch_step_of(lbm_handle* h, const void* src, void* dst, double* fw,
                                  hipStream_t stream) {
   const Grid g = grid_of(h);
   constexpr int NPT = nodes_per_thread<M, ST>();
   if constexpr (NPT > 1) {
-    if (few_waves(h, NPT)) return launch_step_npt<M, ST, SS, CT, 1, FW>(h, g, src, dst, fw, stream);
+    if (few_waves(h, NPT)) return launch_step_npt<M, ST, SS, CT, 1, FW, PAIRED>(h, g, src, dst, fw, stream);
   }
-  return launch_step_npt<M, ST, SS, CT, NPT, FW>(h, g, src, dst, fw, stream);
+  return launch_step_npt<M, ST, SS, CT, NPT, FW, PAIRED>(h, g, src, dst, fw, stream);
 }
 
 }  // namespace lbm

@@ -110,9 +110,7 @@ struct Tile {
 // tiles, y fastest, so that the ring rows that neighbouring tiles share are
 // read through one L2.
 LBM_HD Tile tile_of(const Grid& g, const TwoStep& s, int ty, int b) {
-  constexpr int kXcd = 8;
-  const int xcd = b % kXcd, q = s.nblocks / kXcd, r = s.nblocks % kXcd;
-  int l = xcd * q + (xcd < r ? xcd : r) + b / kXcd;
+  int l = xcd_run_order(b, s.nblocks);
   Tile t;
   const int yt = l % s.nty;
   l /= s.nty;

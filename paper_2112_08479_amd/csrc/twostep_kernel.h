@@ -5,14 +5,14 @@
 // tile of 64 x TY nodes marching in z computes 19 waves of collisions for 16
 // (TY = 8: ten rows and the ring's columns, then eight rows) and reads 1.14
 // times the state. Measured at 1024 x 64 x 128, us per step, single -> paired:
-// cumulant + D3Q7 FP32 391 -> 286, FP64 819 -> 598; BGK + D3Q6 FP32 290 -> 215;
-// cumulant + D3Q27 FP32 655 -> 429, parametrised 657 -> 455. Now the vector
-// units are 64 % busy and the rest goes to the phases between the barriers in
-// which every wave moves data. Measured and not taken: TY = 5 or 3 with two
-// blocks per CU (670 and 890 us per pair against 558), TY = 9 for BGK (440
-// against 398), pulling before the first step's collision (579 against 560),
-// half the waves with their two steps in the other order (the registers spill:
-// 612).
+// cumulant + D3Q7 FP32 391 -> 255, FP64 817 -> 558; cumulant + D3Q27 FP32 661 ->
+// 396, parametrised 663 -> 432; given rates 394 -> 318. The vector units and the
+// phases between the barriers, in which every wave moves data, share the time
+// about evenly (the lean collisions of collide.h took 283 to 255). Measured and
+// not taken: TY = 5 or 3 with two blocks per CU (670 and 890 us per pair against
+// 558), pulling before the first step's collision (579 against 560), half the
+// waves with their two steps in the other order (the registers spill: 612), four
+// or eight chunks in z for two (598 and 630).
 #pragma once
 
 #include "dispatch.h"
@@ -213,7 +213,7 @@ __global__ __launch_bounds__(64 * (TY + 3),
     for (int q = 0; q < LF::Q; ++q) fg[q] = fin[q];
 #pragma unroll
     for (int q = 0; q < LS::Q; ++q) ph[q] = pin[q];
-    collide_node<MODEL, LES, KIND, CT>(fg, ph, p);
+    collide_node<MODEL, LES, KIND, true>(fg, ph, p);
     // all of it before the barriers: none is left over for after them
     keep(fg);
     keep(ph);
@@ -265,7 +265,7 @@ __global__ __launch_bounds__(64 * (TY + 3),
     // bounds and so dropped: the loads in flight are then followed by a known
     // number of stores, and waiting for the loads need not wait for these.
     if (two) {
-      collide_node<MODEL, LES, KIND, CT>(f2, p2, p);
+      collide_node<MODEL, LES, KIND, true>(f2, p2, p);
       store(x2 < g.nx ? out : kDropped);
     } else {
       store(kDropped);
@@ -279,7 +279,7 @@ __global__ __launch_bounds__(64 * (TY + 3),
 template <int M, typename T>
 static hipError_t launch_paired_of(lbm_handle* h, const void* src, void* dst, hipStream_t stream) {
   const Grid g = grid_of(h);
-  if (h->per_launch == 1) return launch_step_npt<M, T, T, T, 1, false, true>(h, g, src, dst, nullptr, stream);
+  if (h->per_launch == 1) return launch_step_of<M, T, T, T, false, true>(h, src, dst, nullptr, stream);
   return with_collision<M>(h, [&](auto les, auto kind) {
     constexpr int TY = two_step_rows(sizeof(T));
     TwoStep ts;
