@@ -4,16 +4,16 @@ Headline workload: the lock exchange on 1024 x 64 x 128 nodes, D3Q27 cumulant
 collision + D3Q7 scalar, Re_b = 30000, Smagorinsky C_s = 0.1, Sc_T = 1,
 g' = 1e-4, FP32 storage and arithmetic (synthetic initial state: step
 function in the concentration with seeded +-1e-3 noise at the gate). A step
-is one update of every node; grids in FP32 take two steps per launch. Also measured on the same
-GPU: FP16 / BF16 storage of the same model on 2048 x 128 x 256 nodes, and
+is one update of every node; cumulant grids in FP32 take two steps per launch.
+Also measured on the same GPU: FP16 / BF16 storage of the same model on 2048 x 128 x 256 nodes, and
 the D3Q19 BGK + Smagorinsky + D3Q6 model on the headline grid.
 
 Timing: W warm-up steps, then K steps between HIP events recorded on the
 stream the kernels run on (torch's current stream, handed to the library).
 MNUPS = nodes * K / seconds / 1e6. Algorithmic HBM bytes per node update:
 one read and one write of every population per launch, 2 * Q * bytes (272 B for
-the cumulant model in FP32) divided by the steps that a launch makes (two in
-FP32 on these grids, one in 16-bit storage). The oracle (FP64, CPU) is timed on a bounded sample.
+the cumulant model in FP32) divided by the steps that a launch makes (two for
+the cumulant grids in FP32, one for BGK and in 16-bit storage). The oracle (FP64, CPU) is timed on a bounded sample.
 """
 import argparse
 import hashlib
@@ -191,7 +191,7 @@ def measure(name, steps, warmup):
     d = lat.diagnostics(raise_unstable=False)
     q = lat.params["q_flow"] + lat.params["q_scalar"]
     es = {"f64": 8, "f32": 4, "f16": 2, "bf16": 2, "bf16_f16s": 2}[w["storage"]]
-    per_launch = 2 if w["storage"] == "f32" and steps >= 2 else 1
+    per_launch = 2 if w["storage"] == "f32" and w["model"] != 1 and steps >= 2 else 1
     bpn = 2 * q * es // per_launch
     n = cfg.n
     lat.close()
