@@ -362,7 +362,7 @@ __global__ void k_zero(double* p, int64_t n) {
 // its blocks stay as full as a row allows.
 static int ablock(const lbm_handle* h) {
   if (h->cfg.parametrized) return block_x(h);
-  return tile_threads(h->cfg.nx, (int64_t)h->cfg.ny * h->cfg.nz, 1);
+  return adjoint_threads(h);
 }
 
 int adjoint_blocks(const lbm_handle* h) {
