@@ -2,7 +2,7 @@
 the sizes where their rules change.
 
 * one step from a random state against the oracle on grids whose buffers lie
-  between the store rule's bounds (23 to 190 MB; 120 in 16-bit storage) and whose
+  between the store rule's bounds (23 to 128 MB; 120 in 16-bit storage) and whose
   rows take an odd number of waves; the bounds are those of the one-step tests:
   2e-7 (FP32), 1e-13 (FP64), half a unit of the stored deviation (FP16);
 * diagnostics, initial diagnostics and wall shear against the same sums taken
@@ -31,7 +31,7 @@ def test_one_step_with_cached_stores(shape, model, storage):
     cfg, P = both(storage, nx=nx, ny=ny, nz=nz, model=model, re_b=2000.0, g_prime=1e-3, cs_smag=0.1)
     f, phi = inputs.near_rest_state(P.flow.Q, P.scal.Q, shape, P.flow.w.numpy(), P.scal.w.numpy(), 5, eps=1e-2)
     lat = pkg.Lattice(cfg)
-    assert (23 << 20) < lat.state_bytes() < ((120 if storage == pkg.F16 else 190) << 20)
+    assert (23 << 20) < lat.state_bytes() < ((120 if storage == pkg.F16 else 128) << 20)
     lat.set_populations(f, phi)
     f0, phi0 = lat.get_populations()
     lat.step(1)
