@@ -196,7 +196,9 @@ int lbm_init_lock_exchange(lbm_handle* h, double lock_fraction, double noise_amp
 int lbm_init_from_field(lbm_handle* h, const double* chi0_dev, double lock_fraction);
 
 /* Queues n time steps (Eq. 17, 28). n = 0 is a no-op; n < 0 is LBM_EINVAL;
- * LBM_ESTATE before initialisation. Does not synchronise. */
+ * LBM_ESTATE before initialisation. Does not synchronise. May be captured into
+ * a graph; an even number of steps, captured or not, leaves the state in the
+ * buffer it was in, so that such a graph can be replayed. */
 int lbm_step(lbm_handle* h, int64_t n);
 
 /* Pre-collision moments of the current state (Eq. 19-20, 27): rho, the

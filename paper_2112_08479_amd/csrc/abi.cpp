@@ -183,6 +183,16 @@ bool two_steps(const lbm_handle* h) {
   return lbm::two_step_pays(g, h->qt, (int)h->esize, h->cu_count);
 }
 
+// Whether a graph knows the handle's buffers from now on: the entry points that
+// only launch kernels may be captured. Handles of single steps never rename
+// their buffers and need not ask.
+void note_capture(lbm_handle* h) {
+  if (!h->paired || h->pinned) return;
+  hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(h->stream, &s) != hipSuccess) (void)hipGetLastError();
+  h->pinned = s == hipStreamCaptureStatusActive;
+}
+
 int set_device(lbm_handle* h) {
   HIPCHECK(hipSetDevice(h->device));
   return LBM_OK;
@@ -498,6 +508,7 @@ int lbm_create(const lbm_config* cfg, void* dev_workspace, size_t bytes, void* h
   h->step = 0;
   h->paired = two_steps(h);
   h->per_launch = 1;
+  h->pinned = false;
   h->initialised = false;
   h->x0 = (int)floor(0.125 * cfg->nx);
   *out = h;
@@ -538,6 +549,7 @@ int lbm_init_lock_exchange(lbm_handle* h, double lock_fraction, double noise_amp
   if (rc) return rc;
   h->cur = 0;
   h->x0 = (int)floor(lock_fraction * h->cfg.nx);
+  note_capture(h);
   HIPCHECK(lbm::launch_init_lock(h, lock_fraction, noise_amp, seed));
   return after_init(h);
 }
@@ -550,6 +562,7 @@ int lbm_init_from_field(lbm_handle* h, const double* chi0_dev, double lock_fract
   if (rc) return rc;
   h->cur = 0;
   h->x0 = (int)floor(lock_fraction * h->cfg.nx);
+  note_capture(h);
   HIPCHECK(lbm::launch_init_field(h, chi0_dev));
   return after_init(h);
 }
@@ -561,14 +574,28 @@ int lbm_step(lbm_handle* h, int64_t n) {
   if (n == 0) return LBM_OK;
   rc = set_device(h);
   if (rc) return rc;
+  note_capture(h);
+  // n single steps leave the state in the buffer n & 1 away, and so do pairs:
+  // a graph that was captured, or is being captured, reads and writes the
+  // buffers of its launches again, after whatever steps came in between. An odd
+  // number of pairs ends elsewhere. Where no graph knows the buffers they change
+  // their names; else the last pair is made as two steps.
+  int64_t pairs = h->paired ? n / 2 : 0;
+  const bool odd = (pairs & 1) != 0;
+  if (odd && h->pinned) --pairs;
   for (int64_t i = 0; i < n;) {
-    h->per_launch = h->paired && n - i >= 2 ? 2 : 1;
+    h->per_launch = pairs > 0 ? 2 : 1;
+    --pairs;
     HIPCHECK(lbm::launch_step(h, h->buf[h->cur], h->buf[h->cur ^ 1]));
     h->cur ^= 1;
     h->step += h->per_launch;
     i += h->per_launch;
   }
   h->per_launch = 1;
+  if (odd && !h->pinned) {
+    std::swap(h->buf[0], h->buf[1]);
+    h->cur ^= 1;
+  }
   return LBM_OK;
 }
 
@@ -578,6 +605,7 @@ int lbm_moments(lbm_handle* h, int dtype, void* rho, void* ux, void* uy, void* u
   if (dtype != LBM_OUT_F32 && dtype != LBM_OUT_F64) return fail(LBM_EINVAL, "dtype must be LBM_OUT_F32 or LBM_OUT_F64");
   rc = set_device(h);
   if (rc) return rc;
+  note_capture(h);
   HIPCHECK(lbm::launch_moments(h, dtype, rho, ux, uy, uz, chi));
   return LBM_OK;
 }
@@ -589,6 +617,7 @@ int lbm_wall_shear(lbm_handle* h, int dtype, void* tau, void* tau_bar) {
   if (h->cfg.nz < 2) return fail(LBM_EINVAL, "the wall shear stress needs nz >= 2");
   rc = set_device(h);
   if (rc) return rc;
+  note_capture(h);
   HIPCHECK(lbm::launch_wall_shear(h, dtype, tau, tau_bar));
   return LBM_OK;
 }

@@ -31,6 +31,7 @@ struct lbm_handle {
   int64_t step;
   bool paired;        // the grid takes steps two at a time
   int per_launch;     // steps that the next launch makes where it is: 1 or 2
+  bool pinned;        // a captured graph names the population buffers
   bool initialised;
   int x0;             // gate index
   // the adjoint run's second stream (default priority) and its events, made
