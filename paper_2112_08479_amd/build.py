@@ -12,7 +12,7 @@ import tempfile
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblbm.so")
-SOURCES = ["abi.cpp", "step.cpp", "step_m0.hip", "step_m1.hip", "step_m2.hip", "step16_m0.hip", "step16_m1.hip",
+SOURCES = ["abi.cpp", "copy.cpp", "step.cpp", "step_m0.hip", "step_m1.hip", "step_m2.hip", "step16_m0.hip", "step16_m1.hip",
            "step16_m2.hip", "stepfw.hip", "pair_m0_f32.hip", "pair_m0_f64.hip", "pair_m1_f64.hip",
            "pair_m2_f32.hip", "init.hip", "observe.hip", "kernels.hip",
            "adjoint.hip", "util.hip"]

@@ -1,4 +1,4 @@
-// Test hooks (populations in and out), the static scratch and state copies.
+// Test hooks (populations in and out) and the static scratch.
 //
 // State convention. A population buffer holds post-collision values at the
 // node where they were produced. One step pulls them (the gather with
@@ -10,7 +10,6 @@
 // permutation.
 #include <math.h>
 
-#include <algorithm>
 #include <mutex>
 
 #include "dispatch.h"
@@ -175,23 +174,6 @@ hipError_t launch_set_pop(lbm_handle* h, int a, const double* src) {
       return hipGetLastError();
     });
   });
-}
-
-// Both sides are device memory of the handle's own GPU unless the caller's slot
-// is not, which the runtime's copy handles. The library's copy moves 2 GiB at
-// 6.3 TB/s (read + write), the runtime's 4.5 GB state at 4.3.
-hipError_t launch_copy_state(lbm_handle* h, const void* src, void* dst) {
-  auto here = [&](const void* p) {
-    hipPointerAttribute_t a;
-    if (hipPointerGetAttributes(&a, p) != hipSuccess) {
-      (void)hipGetLastError();
-      return false;
-    }
-    return a.type == hipMemoryTypeDevice && a.device == h->device && ((uintptr_t)p & 15) == 0;
-  };
-  if (h->state_bytes % 16 == 0 && here(src) && here(dst))
-    return launch_stream_copy(dst, src, h->state_bytes, h->stream);
-  return hipMemcpyAsync(dst, src, h->state_bytes, hipMemcpyDeviceToDevice, h->stream);
 }
 
 }  // namespace lbm

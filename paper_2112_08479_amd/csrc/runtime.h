@@ -116,8 +116,6 @@ inline size_t diag_partials(int nx, int nxb, int nz) {
 // kernels.hip
 hipError_t launch_get_pop(lbm_handle* h, int q, double* dst);
 hipError_t launch_set_pop(lbm_handle* h, int q, const double* src);
-hipError_t launch_copy_state(lbm_handle* h, const void* src, void* dst);
-hipError_t launch_stream_copy(void* dst, const void* src, size_t bytes, hipStream_t stream);
 // device address, on the current device, of the static scratch array of the
 // allocation-free diagnostics (kStaticScratchDoubles doubles: the grids that
 // the entry point takes, whose span means and 8 doubles per 256 columns fit
@@ -125,6 +123,10 @@ hipError_t launch_stream_copy(void* dst, const void* src, size_t bytes, hipStrea
 // columns' maxima that the kernels keep)
 constexpr size_t kStaticScratchDoubles = ((size_t)1 << 22) + ((size_t)1 << 20);
 hipError_t static_scratch(double** ptr);
+// copy.cpp
+hipError_t launch_copy_state(lbm_handle* h, const void* src, void* dst);
+// util.hip
+hipError_t launch_stream_copy(void* dst, const void* src, size_t bytes, hipStream_t stream);
 
 // adjoint.hip
 int adjoint_blocks(const lbm_handle* h);
