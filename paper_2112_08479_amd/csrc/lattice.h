@@ -259,14 +259,16 @@ LBM_HD int xcd_run_order(int b, int nblocks) {
 //   srcp: its x - 1 neighbour (pull of c_x = +1), the node itself at x = 0;
 //   srcm: its x + 1 neighbour (pull of c_x = -1), the node itself at x = nx - 1.
 // At the walls the neighbour is replaced by bounce-back afterwards, so every
-// address stays inside the row.
+// address stays inside the row. xb0: the x-block that the offsets count from, at
+// most the tile's first; a kernel whose pointers already stand there takes rows
+// of any length (a whole row's offset passes 2^31 from 2^31 / QT nodes on).
 template <int QT, int NPT>
 struct TileLanes {
   int own[NPT], srcp[NPT], srcm[NPT], x[NPT];
 };
 
 template <int QT, int NPT>
-LBM_HD TileLanes<QT, NPT> tile_lanes(const Grid& g, int x0, int tid, int bdim) {
+LBM_HD TileLanes<QT, NPT> tile_lanes(const Grid& g, int x0, int tid, int bdim, int xb0 = 0) {
   TileLanes<QT, NPT> t;
   constexpr int XBLK = QT * kXB;
 #pragma unroll
@@ -274,7 +276,7 @@ LBM_HD TileLanes<QT, NPT> tile_lanes(const Grid& g, int x0, int tid, int bdim) {
     const int x = x0 + tid + k * bdim;
     const int xe = x < g.nx ? x : g.nx - 1;
     const int xl = xe & (kXB - 1);
-    const int own = (xe >> kXBShift) * XBLK + xl;
+    const int own = ((xe >> kXBShift) - xb0) * XBLK + xl;
     t.x[k] = x;
     t.own[k] = own;
     t.srcp[k] = xe == 0 ? own : (xl == 0 ? own - XBLK + (kXB - 1) : own - 1);

@@ -25,7 +25,9 @@ __global__ __launch_bounds__(kBlock) void k_moments(const ST* __restrict__ src, 
   const int x0 = (b - row * nbx) * (int)blockDim.x;
   if (x0 + (int)threadIdx.x >= g.nx) return;
   const int y = row % g.ny, z = row / g.ny;
-  const TileLanes<QT, 1> t = tile_lanes<QT, 1>(g, x0, (int)threadIdx.x, (int)blockDim.x);
+  const int xb0 = x0 >> kXBShift;
+  const TileLanes<QT, 1> t = tile_lanes<QT, 1>(g, x0, (int)threadIdx.x, (int)blockDim.x, xb0);
+  src += (int64_t)xb0 * (QT * kXB);
   CT fg[1][LF::Q], ph[1][LS::Q];
   gather_rows<LF, LS, 1, ST, CT, SS>(src, g, t, y, z, fg, ph);
   NodeSums s;
@@ -56,7 +58,8 @@ __global__ __launch_bounds__(kBlock) void k_wall_shear(const ST* __restrict__ sr
   const int b = (int)blockIdx.x * (kBlock / 64) + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   if (b >= g.nxb * g.ny) return;
   const int y = b / g.nxb, xb = b - y * g.nxb;
-  const TileLanes<QT, 1> t = tile_lanes<QT, 1>(g, xb * kXB, lane, 64);
+  const TileLanes<QT, 1> t = tile_lanes<QT, 1>(g, xb * kXB, lane, 64, xb);
+  src += (int64_t)xb * (QT * kXB);
   const int x = t.x[0];
   const bool wall = __builtin_amdgcn_ballot_w64(x == 0 || x == g.nx - 1) != 0;
   double u[2];
@@ -94,7 +97,9 @@ __global__ __launch_bounds__(kDiagThreads) void k_diag_columns(const ST* __restr
   using LS = typename ModelT<MODEL>::LS;
   constexpr int QT = LF::Q + LS::Q;
   const int b = xcd_row_order(blockIdx.x, gridDim.x, g.nxb);
-  const TileLanes<QT, 1> t = tile_lanes<QT, 1>(g, (b % g.nxb) * kXB, (int)threadIdx.x & 63, 64);
+  const int xb = b % g.nxb;
+  const TileLanes<QT, 1> t = tile_lanes<QT, 1>(g, xb * kXB, (int)threadIdx.x & 63, 64, xb);
+  src += (int64_t)xb * (QT * kXB);
   column_sums(g, gp, chibar, partials, [&](int, int y, int z, NodeSums& s) {
     CT fg[1][LF::Q], ph[1][LS::Q];
     gather_rows<LF, LS, 1, ST, CT, SS>(src, g, t, y, z, fg, ph);
