@@ -7,11 +7,13 @@
 namespace lbm {
 
 // at most 8 waves per x-block and z, which share its span rows: enough loads in
-// flight on small grids, and a grid of any span keeps them busy
+// flight on small grids, and a grid of any span keeps them busy. A launch holds
+// fewer than 2^32 threads.
 constexpr int kDiagThreads = 512;
 static inline int diag_threads(const Grid& g) {
+  const int64_t threads = (int64_t)g.nxb * g.nz * 64;
   int w = 1;
-  while (w < 8 && w < g.ny) w *= 2;
+  while (w < 8 && w < g.ny && threads * (2 * w) < ((int64_t)1 << 32)) w *= 2;
   return 64 * w;
 }
 

@@ -1,6 +1,7 @@
 """Host checks of the reporting kernels at the far ends of the grids that
 lbm_create takes (no GPU): tests/report_rows_check.cpp runs the addressing of
-csrc/lattice.h for rows whose offsets pass 32 bits."""
+csrc/lattice.h for rows whose offsets pass 32 bits, tests/diag_launch_check.cpp
+the size of the diagnostics' launch."""
 import os
 import shutil
 import subprocess
@@ -30,3 +31,8 @@ def run(source):
 @pytest.mark.timeout(300)
 def test_rows_beyond_32_bit_offsets():
     run("report_rows_check.cpp")
+
+
+@pytest.mark.timeout(300)
+def test_diagnostics_launch_size():
+    run("diag_launch_check.cpp")
