@@ -47,20 +47,16 @@ __global__ __launch_bounds__(kBlock) void k_moments(const ST* __restrict__ src, 
 // the half-way wall of the quadratic through u = 0 at the wall and the nodes at
 // distances 1/2 and 3/2, tau_w = nu0 (9 u_x(z=0) - u_x(z=1)) / 3, from the
 // pre-collision u_x = j_x / rho of the two nodes. One wavefront per x-block and
-// span row, so that the whole wall is in flight at once (1024 x 64, 16-bit: 188 ->
-// 10 us with the span mean); tw (ny x nx, FP64) keeps the values for the mean.
-template <int MODEL, typename ST, typename CT, typename OT>
-__global__ __launch_bounds__(kBlock) void k_wall_shear(const ST* __restrict__ src, Grid g, double nu0,
-                                                       double* __restrict__ tw, void* tau) {
+// span row, so that the whole wall is in flight at once.
+template <int MODEL, typename ST, typename CT>
+__device__ __forceinline__ double wall_value(const ST* __restrict__ src, const Grid& g, int xb, int y,
+                                             double nu0, int& x) {
   using LF = typename ModelT<MODEL>::LF;
   constexpr int QT = LF::Q + ModelT<MODEL>::LS::Q;
   const int lane = (int)threadIdx.x & 63;
-  const int b = (int)blockIdx.x * (kBlock / 64) + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  if (b >= g.nxb * g.ny) return;
-  const int y = b / g.nxb, xb = b - y * g.nxb;
   const TileLanes<QT, 1> t = tile_lanes<QT, 1>(g, xb * kXB, lane, 64, xb);
   src += (int64_t)xb * (QT * kXB);
-  const int x = t.x[0];
+  x = t.x[0];
   const bool wall = __builtin_amdgcn_ballot_w64(x == 0 || x == g.nx - 1) != 0;
   double u[2];
 #pragma unroll
@@ -71,10 +67,41 @@ __global__ __launch_bounds__(kBlock) void k_wall_shear(const ST* __restrict__ sr
     flow_sums<LF>(fg[0], s);
     u[z] = s.jx / (1.0 + s.drho);
   }
+  return nu0 * (9.0 * u[0] - u[1]) / 3.0;
+}
+
+// Any wall; tw (ny x nx, FP64) keeps the values for the mean, which a second
+// launch takes (1024 x 64, 16-bit: 188 -> 10 us for both).
+template <int MODEL, typename ST, typename CT, typename OT>
+__global__ __launch_bounds__(kBlock) void k_wall_shear(const ST* __restrict__ src, Grid g, double nu0,
+                                                       double* __restrict__ tw, void* tau) {
+  const int b = (int)blockIdx.x * (kBlock / 64) + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  if (b >= g.nxb * g.ny) return;
+  const int y = b / g.nxb;
+  int x;
+  const double v = wall_value<MODEL, ST, CT>(src, g, b - y * g.nxb, y, nu0, x);
   if (x >= g.nx) return;
-  const double v = nu0 * (9.0 * u[0] - u[1]) / 3.0;
   tw[(int64_t)y * g.nx + x] = v;
   put_out<OT>(tau, (int64_t)y * g.nx + x, v);
+}
+
+// A wall of few span rows in one launch: a block holds an x-block's rows, one
+// wave each, and its first wave takes the mean of the values in LDS.
+constexpr int kWallRows = 8;
+template <int MODEL, typename ST, typename CT, typename OT>
+__global__ __launch_bounds__(kWallRows * 64) void k_wall_shear_rows(const ST* __restrict__ src, Grid g,
+                                                                    double nu0, void* tau, void* tau_bar) {
+  __shared__ double tw[kWallRows * kXB];
+  const int y = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = (int)threadIdx.x & 63;
+  int x;
+  const double v = wall_value<MODEL, ST, CT>(src, g, (int)blockIdx.x, y, nu0, x);
+  tw[threadIdx.x] = v;
+  if (x < g.nx) put_out<OT>(tau, (int64_t)y * g.nx + x, v);
+  __syncthreads();
+  if (y != 0 || x >= g.nx) return;
+  double s = 0;
+  for (int r = 0; r < g.ny; ++r) s += tw[r * kXB + lane];
+  put_out<OT>(tau_bar, x, s / g.ny);
 }
 
 // span mean (the integrand of Eq. 66), rows in order
@@ -243,31 +270,34 @@ hipError_t launch_moments(lbm_handle* h, int dtype, void* rho, void* ux, void* u
   });
 }
 
+// The mean in the same launch where a block holds the whole span: a second launch
+// costs 2 us (64 x 4 BGK FP32: 6.3 us with the mean, 8.5 in two launches).
 hipError_t launch_wall_shear(lbm_handle* h, int dtype, void* tau, void* tau_bar) {
   const Grid g = grid_of(h);
   const int64_t waves = (int64_t)g.nxb * g.ny;
   const unsigned blocks = (unsigned)((waves + kBlock / 64 - 1) / (kBlock / 64));
   const double nu0 = h->prm.nu0;
-  const bool f64 = dtype == LBM_OUT_F64;
-  const hipError_t e = with_model(h, [&](auto mc) {
-    constexpr int M = decltype(mc)::value;
-    return with_storage(h, [&](auto st, auto, auto ct) {
-      using ST = decltype(st);
-      using CT = decltype(ct);
-      const ST* s = static_cast<const ST*>(h->buf[h->cur]);
-      if (f64)
-        hipLaunchKernelGGL((k_wall_shear<M, ST, CT, double>), dim3(blocks), dim3(kBlock), 0, h->stream, s, g, nu0, h->scratch, tau);
-      else
-        hipLaunchKernelGGL((k_wall_shear<M, ST, CT, float>), dim3(blocks), dim3(kBlock), 0, h->stream, s, g, nu0, h->scratch, tau);
-      return hipGetLastError();
+  const bool rows = tau_bar && g.ny <= kWallRows;
+  auto launch = [&](auto out) {
+    using OT = decltype(out);
+    const hipError_t e = with_model(h, [&](auto mc) {
+      constexpr int M = decltype(mc)::value;
+      return with_storage(h, [&](auto st, auto, auto ct) {
+        using ST = decltype(st);
+        using CT = decltype(ct);
+        const ST* s = static_cast<const ST*>(h->buf[h->cur]);
+        if (rows)
+          hipLaunchKernelGGL((k_wall_shear_rows<M, ST, CT, OT>), dim3(g.nxb), dim3(64 * g.ny), 0, h->stream, s, g, nu0, tau, tau_bar);
+        else
+          hipLaunchKernelGGL((k_wall_shear<M, ST, CT, OT>), dim3(blocks), dim3(kBlock), 0, h->stream, s, g, nu0, h->scratch, tau);
+        return hipGetLastError();
+      });
     });
-  });
-  if (e != hipSuccess || !tau_bar) return e;
-  if (f64)
-    hipLaunchKernelGGL((k_span_mean<double>), dim3(g.nxb), dim3(64), 0, h->stream, h->scratch, g, tau_bar);
-  else
-    hipLaunchKernelGGL((k_span_mean<float>), dim3(g.nxb), dim3(64), 0, h->stream, h->scratch, g, tau_bar);
-  return hipGetLastError();
+    if (e != hipSuccess || !tau_bar || rows) return e;
+    hipLaunchKernelGGL((k_span_mean<OT>), dim3(g.nxb), dim3(64), 0, h->stream, h->scratch, g, tau_bar);
+    return hipGetLastError();
+  };
+  return dtype == LBM_OUT_F64 ? launch(double{}) : launch(float{});
 }
 
 hipError_t launch_diag_reduce(lbm_handle* h, double* out) {
