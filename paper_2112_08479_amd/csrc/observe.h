@@ -81,7 +81,7 @@ __device__ void block_reduce(double (&v)[NV], int imax) {
 
 // Bound by reading the state: 1024 x 64 x 128 FP32 233 -> 185 us (6.2 TB/s), bf16
 // 185 -> 130 (4.4), 128 x 8 x 16 FP64 16 -> 9, against one thread per column with
-// 64-bit addresses per population, a square root and three divisions per node.
+// 64-bit addresses per population and a square root per node.
 // One block per x-block and z; its waves take the span rows in turn. node(x, y,
 // z, sums) gives a node's moments; it is called by every lane of a wave, with x
 // held inside the grid. Writes the span mean of chi, and the block's partial
@@ -102,8 +102,8 @@ __device__ __forceinline__ void column_sums(const Grid& g, double gp, double* __
     NodeSums s;
     node(x < g.nx ? x : g.nx - 1, y, z, s);
     if (x < g.nx) {
-      const double r = 1.0 + s.drho, ir = 1.0 / r;
-      const double ux = s.jx * ir, uy = s.jy * ir, uz = (s.jz - 0.5 * gp * s.c) * ir;
+      const double r = 1.0 + s.drho;
+      const double ux = s.jx / r, uy = s.jy / r, uz = (s.jz - 0.5 * gp * s.c) / r;
       const bool fin = isfinite(r) && isfinite(s.c) && isfinite(ux) && isfinite(uy) && isfinite(uz);
       v[0] += s.drho;
       col += s.c;

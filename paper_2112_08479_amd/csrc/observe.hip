@@ -34,11 +34,11 @@ __global__ __launch_bounds__(kBlock) void k_moments(const ST* __restrict__ src, 
   flow_sums<LF>(fg[0], s);
   static_for<0, LS::Q>([&](auto qc) { s.c += to_d(ph[0][decltype(qc)::value]); });
   const int64_t node = (int64_t)row * g.nx + t.x[0];
-  const double r = 1.0 + s.drho, ir = 1.0 / r;
+  const double r = 1.0 + s.drho;
   put_out<OT>(rho, node, r);
-  put_out<OT>(ux, node, s.jx * ir);
-  put_out<OT>(uy, node, s.jy * ir);
-  put_out<OT>(uz, node, (s.jz - 0.5 * gp * s.c) * ir);
+  put_out<OT>(ux, node, s.jx / r);
+  put_out<OT>(uy, node, s.jy / r);
+  put_out<OT>(uz, node, (s.jz - 0.5 * gp * s.c) / r);
   put_out<OT>(chi, node, s.c);
 }
 
