@@ -359,10 +359,15 @@ __global__ void k_zero(double* p, int64_t n) {
 
 // ---------------------------------------------------------------- launchers
 // The parametrised kernel's LDS holds a column per thread of a full block, so
-// its blocks stay as full as a row allows.
+// its blocks stay as full as a row allows. The others take the step's blocks, for
+// rows of three waves too: whole rows (192 threads) are faster on a few grids whose
+// rows fill the CUs evenly (100 steps, cumulant + D3Q27 FP32: 185 x 16 x 24 2.99 ms
+// against 3.14, 192 x 16 x 32 3.44 against 3.52) and slower on the others (180 x 24 x
+// 24 4.42 against 3.75, 160 x 40 x 40 8.41 against 7.59, 129 x 30 x 50 7.55 against
+// 7.27; cumulant + D3Q7 FP64 150 x 20 x 60 8.07 against 7.30).
 static int ablock(const lbm_handle* h) {
   if (h->cfg.parametrized) return block_x(h);
-  return adjoint_threads(h);
+  return tile_threads(h->cfg.nx, (int64_t)h->cfg.ny * h->cfg.nz, 1);
 }
 
 int adjoint_blocks(const lbm_handle* h) {

@@ -80,18 +80,6 @@ static inline int block_x(const lbm_handle* h) {
   return nx >= kBlock ? kBlock : ((nx + 63) / 64) * 64;
 }
 
-// Threads of the adjoint's forward and reverse steps (one node each): those of
-// tile_threads, but rows of three waves go out whole in FP32, where the two
-// streams share the chip (185 x 16 x 24 cumulant + D3Q27, 103 steps: 3.46 ms
-// against 3.55 in blocks of one wave, and no gain if only one of the two takes
-// them; cumulant + D3Q7 the same; FP64 5.64 against 5.58; 384 x 24 x 40 in blocks
-// of three waves 4.02 against 3.85).
-static inline int adjoint_threads(const lbm_handle* h) {
-  const int64_t rows = (int64_t)h->cfg.ny * h->cfg.nz;
-  if (h->cfg.storage != LBM_F64 && xblocks(h->cfg.nx) == 3 && 3 * rows > 512) return 3 * kXB;
-  return tile_threads(h->cfg.nx, rows, 1);
-}
-
 template <typename CT>
 static inline Phys<CT> phys_of(const lbm_handle* h) {
   const lbm_params& p = h->prm;
