@@ -206,19 +206,21 @@ LBM_HD int tile_threads(int nx, int64_t rows, int npt) {
   return w % 4 == 0 ? 256 : (w % 2 == 0 ? 128 : 64);
 }
 
-// Whether a step's results leave past the caches. Two buffers that the 256 MB
-// last-level cache holds together (128 MiB each) are read back from it by the
-// next step, and plain stores put them there; buffers of a few MB, and those
-// beyond the cache, are faster out of the way. Measured, us per step past the
-// caches / plain: 9 MB 6.4 / 7.3, 17.8 MB 8.8 / 9.9, 28 MB 13.3 / 11.0, 35 MB
-// 15.8 / 11.9, 73 MB 26.5 / 20.0, 105 MB 38.4 / 27.6; BGK FP32 128 MB 54.9 / 41.4,
-// 141 MB 60.4 / 63.4, 195 MB 74.4 / 83.0 (rows of 512 at 139 MB 52.4 / 49.9); pairs
-// FP32 175 MB 48.9 / 52.8, FP64 180 MB 49.8 / 53.8; cumulant + D3Q27 FP64 155 MB
-// 61.7 / 58.6, 188 MB 74.0 / 73.3; 285 MB 104 / 110; 16-bit elements 71 MB 30.2 /
-// 27.8, 113 MB 46.0 / 43.9, 139 MB 53.2 / 56.2.
-inline bool stores_past_caches(size_t state_bytes, size_t element_bytes) {
-  return state_bytes < ((size_t)23 << 20) ||
-         state_bytes > ((size_t)(element_bytes == 2 ? 120 : 128) << 20);
+// Whether a step's results leave past the caches. Plain stores leave them in the
+// 256 MB last-level cache, where the next step reads them, as long as the two
+// buffers fit it together: up to 128 MiB each, whatever the elements. Measured, us
+// per step, past the caches / plain: cumulant + D3Q7 FP32 28 MiB 14.2 / 11.6, 73 MB
+// 26.5 / 20.0, 105 MB 38.4 / 27.6; 16-bit elements 122 MiB 51.2 / 49.9 (BGK 51.2 / 48.4),
+// 126 MiB 53.1 / 52.4 (52.6 / 49.6), 130 MiB 53.8 / 56.1 (55.2 / 57.6); BGK FP32 128 MB
+// 54.9 / 41.4, 141 MB 60.4 / 63.4, 195 MB 74.4 / 83.0; pairs FP32 175 MB 48.9 / 52.8,
+// FP64 180 MB 49.8 / 53.8; 285 MB 104 / 110.
+// Small buffers are the other way round: two of 16 MiB fill the eight 4 MB L2s, and
+// what a step leaves there is written back when it ends. The crossing lies at 16 to
+// 20 MiB (cumulant + D3Q7 FP32 16 MiB 8.4 / 9.3, 20 MiB 11.0 / 9.9; BGK FP64 8.2 / 8.9,
+// 9.9 / 9.3) and for the FP64 form with 54 populations at 20 to 24 MiB (10.3 / 10.8,
+// 12.8 / 11.3), which set the line.
+inline bool stores_past_caches(size_t state_bytes) {
+  return state_bytes < ((size_t)23 << 20) || state_bytes > ((size_t)128 << 20);
 }
 
 // Block order of the row-tiled kernels. Consecutive block ids are dealt

@@ -107,7 +107,7 @@ static hipError_t launch_step_npt(lbm_handle* h, const Grid& g, const void* src,
     if constexpr (FW && KIND == kCumGeneral) {  // not differentiated
       return hipErrorInvalidValue;
     } else {
-      if (stores_past_caches(h->state_bytes, h->esize))
+      if (stores_past_caches(h->state_bytes))
         hipLaunchKernelGGL((k_step<M, ST, SS, CT, LES, KIND, NPT, FW, PAIRED, true>), dim3(blocks), dim3(bx), 0, st, s, d, g, p, nbx, fw);
       else
         hipLaunchKernelGGL((k_step<M, ST, SS, CT, LES, KIND, NPT, FW, PAIRED, false>), dim3(blocks), dim3(bx), 0, st, s, d, g, p, nbx, fw);

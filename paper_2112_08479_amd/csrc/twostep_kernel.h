@@ -289,7 +289,7 @@ static hipError_t launch_paired_of(lbm_handle* h, const void* src, void* dst, hi
                          dim3(ts.nblocks), dim3(64 * (TY + 3)), 0, stream, static_cast<const T*>(src),
                          static_cast<T*>(dst), g, phys_of<T>(h), ts);
     };
-    if (stores_past_caches(h->state_bytes, h->esize))
+    if (stores_past_caches(h->state_bytes))
       launch(std::true_type{});
     else
       launch(std::false_type{});
