@@ -419,11 +419,16 @@ hipError_t launch_adjoint_step(lbm_handle* h, const void* state, const void* lam
     };
     using Y = std::true_type;
     using N = std::false_type;
-    // lambda is read back by the next launch, beside a state of the same size:
-    // plain stores while the last-level cache holds them (400 x 24 x 50 FP32, 73
-    // MB a buffer: 100 steps in 8.4 ms against 8.55 past the caches), past the
-    // caches beyond (146 MB 10.1 against 9.7, 1141 MB 52.3 against 50.2)
-    const bool nt = h->state_bytes > ((size_t)120 << 20);
+    // lambda is read back by the next launch. A reverse step touches three buffers
+    // (a state, both lambdas), the next one two of them again: plain stores win
+    // while the 256 MB last-level cache holds somewhat more than two. Measured, ms
+    // per 100 steps with every 25th kept, plain / past the caches: cumulant + D3Q7
+    // FP32 88 MiB a buffer 11.25 / 11.46, 104 13.21 / 13.18, 112 14.33 / 14.11, 120
+    // 15.31 / 14.95; BGK FP32 104 12.83 / 12.88, 112 14.10 / 13.82; BGK FP64 104 13.05 /
+    // 13.20, 113 14.38 / 14.18. The kernels with more live data turn earlier:
+    // cumulant + D3Q27 FP32 at 85 MiB (104 14.21 / 13.94), cumulant + D3Q7 FP64 below
+    // 64 (10.00 / 9.77 at 72).
+    const bool nt = h->state_bytes > ((size_t)108 << 20);
     if constexpr (M != 1) {
       if (h->cfg.parametrized) {  // never with the LES
         nt ? launch(N{}, Y{}, Y{}) : launch(N{}, Y{}, N{});
