@@ -180,7 +180,11 @@ bool two_steps(const lbm_handle* h) {
   const bool f64 = c.storage == LBM_F64 && c.model != LBM_CUMULANT27_FCM27;
   if (!f32 && !f64) return false;
   const lbm::Grid g{c.nx, c.ny, c.nz, h->n, lbm::xblocks(c.nx)};
-  return lbm::two_step_pays(g, h->qt, (int)h->esize, h->cu_count);
+  using lbm::Rates;
+  const bool unit = c.model == LBM_BGK19_SMAG_Q6 ||
+                    (c.omega3 == 1.0 && c.omega4 == 1.0 && c.omega5 == 1.0 && c.omega6 == 1.0);
+  const Rates rates = c.parametrized ? Rates::kParametrised : (unit ? Rates::kUnit : Rates::kGiven);
+  return lbm::two_step_pays(g, h->qt, (int)h->esize, h->cu_count, rates, h->state_bytes);
 }
 
 // Whether a graph knows the handle's buffers from now on: the entry points that

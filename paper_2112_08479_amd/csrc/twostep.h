@@ -82,24 +82,46 @@ inline int64_t two_step_plan(const Grid& g, int ty, int cus, TwoStep& s) {
   return best;
 }
 
+// Plane iterations that a pair may spend per one that the grid needs and still be
+// no slower than two single steps, by collision. Break-even is the gain of a pair
+// (40 steps, single / paired) times spent / work, measured on some 45 grids each on
+// both sides of the line: cumulant with unit rates + D3Q7 FP32 2.0 to 2.9, FP64 2.1 to
+// 2.9, + D3Q27 FP32 1.9 to 2.5; parametrised 1.9 to 2.7, 1.9 to 3.2 and 1.7 to 2.2; BGK
+// FP64 1.8 to 2.7 (the least of them on large grids, which the other condition of
+// two_step_pays holds to less). The given rates transform forward as well and have
+// less to gain: FP32 + D3Q7 1.5 to 2.2, + D3Q27 1.5 to 1.9; FP64 1.9 to 2.9 where memory
+// feeds the single steps, 1.7 to 2.1 where the last-level cache does. What a line at
+// 1.6 work + 2 alone cost them: 655 x 27 x 93 + D3Q27 127 us per step single, 148 paired;
+// 962 x 19 x 90 + D3Q7 85 / 92; FP64 372 x 29 x 32 31.6 / 35.4.
+enum class Rates { kUnit, kParametrised, kGiven };
+inline double two_step_limit(int qt, int bytes, Rates rates, size_t state_bytes) {
+  if (rates == Rates::kGiven) {
+    if (bytes == 4) return qt == 54 ? 1.5 : 1.67;
+    return state_bytes > ((size_t)128 << 20) ? 2.0 : 1.7;
+  }
+  if (qt == 25) return 1.9;
+  return qt == 54 && rates == Rates::kParametrised ? 1.9 : 2.05;
+}
+
 // Two steps at a time halve the traffic but need a grid whose tiles keep every
 // CU busy, and one that the caches do not hold anyway: `work` is the tile planes
 // per CU if nothing were lost to ragged tiles, chunk ends and a part-filled last
-// round, `spent` those that the plan takes. Measured per step, single against
-// paired (MI355X, cumulant + D3Q7): FP32 256 x 16 x 32 (work 1.0, spent 4) 8.9 /
-// 11.7 us, 400 x 24 x 50 (3.7, 8) 21.8 / 24.4, 448 x 28 x 56 (5.4, 10) 29.5 / 29.7,
-// 512 x 32 x 64 (8, 11) 46.7 / 40.1, 800 x 50 x 100 (30.5, 46) 186 / 179, 1024 x
-// 64 x 128 (64, 67) 391 / 283; FP64 320 x 20 x 40 (3.1, 7) 21.7 / 24.8, 400 x 24 x
-// 50 (5.9, 11) 47.9 / 41.6, 512 x 32 x 64 (12.8, 17) 104 / 80. A pull reaches over
-// three planes with 32-bit offsets, which bounds their size.
-inline bool two_step_pays(const Grid& g, int qt, int bytes, int cus) {
+// round, `spent` those that the plan takes. Single against paired, us per step:
+// cumulant + D3Q7 FP32 277 x 23 x 41 (work 2.0, spent 6) 13.8 / 15.1, 427 x 23 x 47 (3.5,
+// 7) 20.3 / 18.8, 512 x 32 x 64 (8, 11) 55 / 38, 1024 x 64 x 128 (64, 67) 394 / 255; FP64
+// 186 x 33 x 40 (3.0, 7) 21.9 / 22.6, 372 x 29 x 32 (4.2, 8) 30.6 / 28.2, 1024 x 64 x 128 819 /
+// 560; cumulant + D3Q27 FP32 389 x 11 x 106 (3.5, 9) 34.3 / 35.8, 423 x 33 x 56 (6.0, 11)
+// 61.9 / 53.5, 1024 x 64 x 128 656 / 401; BGK FP64 335 x 40 x 25 (4.1, 8) 22.0 / 22.6, 381 x 13
+// x 105 (6.4, 11) 33.0 / 31.1, 1024 x 64 x 128 599 / 443. A pull reaches over three planes
+// with 32-bit offsets, which bounds their size.
+inline bool two_step_pays(const Grid& g, int qt, int bytes, int cus, Rates rates, size_t state_bytes) {
   const int64_t plane = (int64_t)g.ny * g.nxb * kXB * qt * bytes;
   if (3 * plane >= ((int64_t)1 << 31)) return false;
   const int ty = two_step_rows(bytes);
   TwoStep s;
   const double spent = (double)two_step_plan(g, ty, cus, s);
   const double work = (double)g.n / ((double)kXB * ty * cus);
-  return spent <= 1.6 * work + 2.0;
+  return spent <= 1.6 * work + 2.0 && spent <= two_step_limit(qt, bytes, rates, state_bytes) * work;
 }
 
 struct Tile {
