@@ -12,8 +12,8 @@ Timing: W warm-up steps, then K steps between HIP events recorded on the
 stream the kernels run on (torch's current stream, handed to the library).
 MNUPS = nodes * K / seconds / 1e6. Algorithmic HBM bytes per node update:
 one read and one write of every population per launch, 2 * Q * bytes (272 B for
-the cumulant model in FP32) divided by the steps that a launch makes (two for
-the cumulant grids in FP32, one for BGK and in 16-bit storage). The oracle (FP64, CPU) is timed on a bounded sample.
+the cumulant model in FP32) divided by the steps that a launch makes, which the
+library tells (two for the cumulant grids in FP32, one for BGK and in 16-bit storage). The oracle (FP64, CPU) is timed on a bounded sample.
 """
 import argparse
 import hashlib
@@ -191,8 +191,9 @@ def measure(name, steps, warmup):
     d = lat.diagnostics(raise_unstable=False)
     q = lat.params["q_flow"] + lat.params["q_scalar"]
     es = {"f64": 8, "f32": 4, "f16": 2, "bf16": 2, "bf16_f16s": 2}[w["storage"]]
-    per_launch = 2 if w["storage"] == "f32" and w["model"] != 1 and steps >= 2 else 1
-    bpn = 2 * q * es // per_launch
+    per_launch = lat.steps_per_launch
+    # launches of the timed steps: an odd last step is one of its own
+    bpn = 2 * q * es * (-(-steps // per_launch)) / steps
     n = cfg.n
     lat.close()
     del lat
@@ -334,8 +335,8 @@ def main():
             print(json.dumps({"progress": "adjoint", **r}), file=sys.stderr, flush=True)
             variants.append(r)
     cpu = None if args.no_cpu_baseline else cpu_baseline()
-    launch_bytes = head["bytes_per_node_update"] * head["nodes"]
-    achieved = launch_bytes / (head["ms_per_step"] * 1e-3) / 1e9
+    step_bytes = head["bytes_per_node_update"] * head["nodes"]
+    achieved = step_bytes / (head["ms_per_step"] * 1e-3) / 1e9
     w = WORKLOADS[args.workload]
     line = {
         "metric": "MNUPS (node updates per second / 1e6) of the fused stream-and-collide step",
@@ -358,7 +359,7 @@ def main():
                    "parallelism": "single-gpu"},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS,
-                     "traffic": traffic_for(args.workload, launch_bytes)},
+                     "traffic": traffic_for(args.workload, step_bytes)},
         "cpu_baseline": cpu,
         "stream_copy_GB_per_s": copy["GB_per_s"],
         "variants": variants,

@@ -201,6 +201,11 @@ int lbm_init_from_field(lbm_handle* h, const double* chi0_dev, double lock_fract
  * buffer it was in, so that such a graph can be replayed. */
 int lbm_step(lbm_handle* h, int64_t n);
 
+/* Host only. Time steps that a launch of lbm_step makes on this handle's grid:
+ * 2 where it takes them in pairs (an odd last step is a launch of its own), else
+ * 1. The populations are the same either way. */
+int lbm_steps_per_launch(const lbm_handle* h, int32_t* steps);
+
 /* Pre-collision moments of the current state (Eq. 19-20, 27): rho, the
  * velocity u = (j + F/2)/rho, chi, nx*ny*nz elements each of type dtype
  * (LBM_OUT_F32 / LBM_OUT_F64) into caller device buffers; NULL skips one. */

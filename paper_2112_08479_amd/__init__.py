@@ -32,6 +32,7 @@ EXPORTS = [
     "lbm_wall_shear", "lbm_diagnostics", "lbm_get_step", "lbm_checkpoint_save", "lbm_checkpoint_load",
     "lbm_get_populations", "lbm_set_populations", "lbm_adjoint_workspace_bytes",
     "lbm_adjoint_run", "lbm_stream_copy", "lbm_last_error", "lbm_checkpoint_diagnostics",
+    "lbm_steps_per_launch",
 ]
 
 
@@ -92,6 +93,7 @@ def lib():
             "lbm_wall_shear": (ctypes.c_int, [vp, ctypes.c_int, vp, vp]),
             "lbm_diagnostics": (ctypes.c_int, [vp, ctypes.POINTER(c_diag)]),
             "lbm_get_step": (ctypes.c_int, [vp, ctypes.POINTER(i64)]),
+            "lbm_steps_per_launch": (ctypes.c_int, [vp, ctypes.POINTER(ctypes.c_int32)]),
             "lbm_checkpoint_save": (ctypes.c_int, [vp, vp]),
             "lbm_checkpoint_load": (ctypes.c_int, [vp, vp]),
             "lbm_get_populations": (ctypes.c_int, [vp, vp, vp]),
@@ -221,6 +223,13 @@ class Lattice:
     def step_count(self):
         s = ctypes.c_int64()
         check(self.L.lbm_get_step(self.h, ctypes.byref(s)))
+        return s.value
+
+    @property
+    def steps_per_launch(self):
+        """Steps that a launch makes on this grid: 2 where they go in pairs."""
+        s = ctypes.c_int32()
+        check(self.L.lbm_steps_per_launch(self.h, ctypes.byref(s)))
         return s.value
 
     def moments(self, dtype=OUT_F64):

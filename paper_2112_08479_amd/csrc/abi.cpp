@@ -603,6 +603,12 @@ int lbm_step(lbm_handle* h, int64_t n) {
   return LBM_OK;
 }
 
+int lbm_steps_per_launch(const lbm_handle* h, int32_t* steps) {
+  if (!h || !steps) return fail(LBM_EINVAL, "NULL argument");
+  *steps = h->paired ? 2 : 1;
+  return LBM_OK;
+}
+
 int lbm_moments(lbm_handle* h, int dtype, void* rho, void* ux, void* uy, void* uz, void* chi) {
   int rc = require_ready(h);
   if (rc) return rc;
