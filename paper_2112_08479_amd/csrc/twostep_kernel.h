@@ -21,9 +21,9 @@
 namespace lbm {
 
 // waves per SIMD that the block's registers must allow
-template <typename ST>
+template <typename T>
 constexpr int tile_waves() {
-  return sizeof(ST) == 8 ? 2 : 3;
+  return sizeof(T) == 8 ? 2 : 3;
 }
 // Populations of the next plane that are pulled before the second step is
 // computed: all, and already before the barriers, where the registers hold
@@ -51,10 +51,8 @@ __device__ __forceinline__ T load_at(Rsrc r, uint32_t lane, int scalar) {
   if constexpr (sizeof(T) == 8) {
     typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
     return __builtin_bit_cast(T, (u32x2)__builtin_amdgcn_raw_buffer_load_b64(r, lane, scalar, 0));
-  } else if constexpr (sizeof(T) == 4) {
-    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, lane, scalar, 0));
   } else {
-    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b16(r, lane, scalar, 0));
+    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, lane, scalar, 0));
   }
 }
 // a lane offset beyond every plane (three planes are below 2 GiB)
@@ -65,10 +63,8 @@ __device__ __forceinline__ void store_at(Rsrc r, uint32_t lane, int scalar, T v)
   if constexpr (sizeof(T) == 8) {
     typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
     __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, lane, scalar, kNt);
-  } else if constexpr (sizeof(T) == 4) {
-    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, v), r, lane, scalar, kNt);
   } else {
-    __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, v), r, lane, scalar, kNt);
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, v), r, lane, scalar, kNt);
   }
 }
 
@@ -111,16 +107,16 @@ __device__ __forceinline__ Planes planes_at(const ST* src, const Grid& g, int64_
 // pull of the populations A .. B - 1 of a node of plane z. At a wall the
 // lane's address itself turns to the node's own opposite population, so that
 // these loads fly as freely as the others.
-template <class P, int A, int B, typename ST, typename SS, typename CT, int QF, int QS>
+template <class P, int A, int B, typename T, int QF, int QS>
 __device__ __forceinline__ void pull_plane(const Planes& s, const Grid& g, int z, int x, bool wall,
-                                           const uint32_t (&off)[3][3], CT (&f)[QF], CT (&ph)[QS]) {
-  constexpr int kSeg = kXB * (int)sizeof(ST);
+                                           const uint32_t (&off)[3][3], T (&f)[QF], T (&ph)[QS]) {
+  constexpr int kSeg = kXB * (int)sizeof(T);
   auto load = [&](auto ac, Rsrc r, uint32_t lane, int scalar) __attribute__((always_inline)) {
     constexpr int a = decltype(ac)::value;
     if constexpr (P::flow(a))
-      f[a] = Conv<ST, CT>::load(load_at<ST>(r, lane, scalar));
+      f[a] = load_at<T>(r, lane, scalar);
     else
-      ph[a - QF] = Conv<SS, CT>::load(load_at<SS>(r, lane, scalar));
+      ph[a - QF] = load_at<T>(r, lane, scalar);
   };
   if (!wall) {
     static_for<A, B>([&](auto ac) {
@@ -149,17 +145,16 @@ __device__ __forceinline__ void pull_plane(const Planes& s, const Grid& g, int z
   }
 }
 
-template <int MODEL, typename ST, typename SS, typename CT, bool LES, int KIND, int TY, bool NT>
-__global__ __launch_bounds__(64 * (TY + 3),
-                             tile_waves<ST>()) void k_step2(const ST* __restrict__ src,
-                                                         ST* __restrict__ dst, Grid g, Phys<CT> p,
-                                                         TwoStep ts) {
+template <int MODEL, typename T, bool LES, int KIND, int TY, bool NT>
+__global__ __launch_bounds__(64 * (TY + 3), tile_waves<T>()) void k_step2(const T* __restrict__ src,
+                                                                          T* __restrict__ dst, Grid g,
+                                                                          Phys<T> p, TwoStep ts) {
   using LF = typename ModelT<MODEL>::LF;
   using LS = typename ModelT<MODEL>::LS;
   using P = Pops<LF, LS>;
   constexpr int QT = P::Q;
   static_assert(2 * (TY + 2) <= 64, "the ring's columns share one wave");
-  __shared__ ST lds[P::kSlots * TY * kPitch];
+  __shared__ T lds[P::kSlots * TY * kPitch];
   const int lane = (int)threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const Tile tile = tile_of(g, ts, TY, (int)blockIdx.x);
@@ -170,24 +165,24 @@ __global__ __launch_bounds__(64 * (TY + 3),
   const bool second = w < tile.rows;
   const int x2 = tile.xb * kXB + lane;  // the second step's node, row w of the tile
   const int64_t plane = (int64_t)g.ny * g.nxb * (QT * kXB);
-  const uint32_t bytes = (uint32_t)(plane * (int64_t)sizeof(ST));
+  const uint32_t bytes = (uint32_t)(plane * (int64_t)sizeof(T));
   uint32_t off[3][3];
-  plane_offsets<QT, ST>(g, l.x, l.y, off);
+  plane_offsets<QT, T>(g, l.x, l.y, off);
   const uint32_t out = (uint32_t)(((int64_t)(tile.y0 + w) * g.nxb + tile.xb) * (QT * kXB) + lane) *
-                       (uint32_t)sizeof(ST);
+                       (uint32_t)sizeof(T);
   // LDS places of the lane for the first step's pushes and the second step's
   // reads; the resting class's as well, which lies beyond the reach of an
   // instruction's constant offset (hidden so that no sums are kept instead)
   int at = lds_lane(l, lane), at2 = w * kPitch + 1 + lane;
   int rest = at + class_base<P, TY>(0, 0), rest2 = at2 + class_base<P, TY>(0, 0);
   asm("" : "+v"(at), "+v"(at2), "+v"(rest), "+v"(rest2));
-  CT fin[LF::Q], pin[LS::Q];  // pulled populations of the next plane
-  CT fg[LF::Q], ph[LS::Q];    // the first step's results
+  T fin[LF::Q], pin[LS::Q];  // pulled populations of the next plane
+  T fg[LF::Q], ph[LS::Q];    // the first step's results
   // populations from .. to - 1 of plane k + 1 (the last plane again past the end)
   auto pull = [&](int k, auto from, auto to) __attribute__((always_inline)) {
     const int z = k + 1 < g.nz ? k + 1 : g.nz - 1;
     const Planes s = planes_at(src, g, plane, bytes, z);
-    pull_plane<P, decltype(from)::value, decltype(to)::value, ST, SS, CT>(
+    pull_plane<P, decltype(from)::value, decltype(to)::value, T>(
         s, g, z, l.x, wave_at_wall || z == 0 || z == g.nz - 1, off, fin, pin);
   };
   using I0 = std::integral_constant<int, 0>;
@@ -197,9 +192,9 @@ __global__ __launch_bounds__(64 * (TY + 3),
   auto put = [&](auto ac, int i) __attribute__((always_inline)) {
     constexpr int a = decltype(ac)::value;
     if constexpr (P::flow(a))
-      lds[i] = Conv<ST, CT>::store(fg[a]);
+      lds[i] = fg[a];
     else
-      reinterpret_cast<SS*>(lds)[i] = Conv<SS, CT>::store(ph[a - LF::Q]);
+      lds[i] = ph[a - LF::Q];
   };
   // First step of plane k, up to its downward pushes, and then the pulls of the
   // plane after it, which fly over the barriers and the second step. Every wave
@@ -227,7 +222,7 @@ __global__ __launch_bounds__(64 * (TY + 3),
   for (int k = ks;; ++k) {
     const bool two = second && k > tile.z0;  // second step of plane k - 1
     lds_barrier();
-    CT f2[LF::Q], p2[LS::Q];
+    T f2[LF::Q], p2[LS::Q];
     if (two) {
       int up2 = at2 + class_base<P, TY>(1, k - 1);
       asm("" : "+v"(up2));
@@ -235,9 +230,9 @@ __global__ __launch_bounds__(64 * (TY + 3),
         constexpr int a = decltype(ac)::value;
         const int i = (P::cz(a) < 0 ? at2 : (P::cz(a) > 0 ? up2 : rest2)) + class_offset<P, TY>(a, 0, 0);
         if constexpr (P::flow(a))
-          f2[a] = Conv<ST, CT>::load(lds[i]);
+          f2[a] = lds[i];
         else
-          p2[a - LF::Q] = Conv<SS, CT>::load(reinterpret_cast<const SS*>(lds)[i]);
+          p2[a - LF::Q] = lds[i];
       });
     }
     lds_barrier();
@@ -254,11 +249,11 @@ __global__ __launch_bounds__(64 * (TY + 3),
     auto store = [&](uint32_t to) __attribute__((always_inline)) {
       static_for<0, QT>([&](auto ac) {
         constexpr int a = decltype(ac)::value;
-        constexpr int seg = a * kXB * (int)sizeof(ST);
+        constexpr int seg = a * kXB * (int)sizeof(T);
         if constexpr (P::flow(a))
-          store_at<NT>(rd, to, seg, Conv<ST, CT>::store(f2[a]));
+          store_at<NT>(rd, to, seg, f2[a]);
         else
-          store_at<NT>(rd, to, seg, Conv<SS, CT>::store(p2[a - LF::Q]));
+          store_at<NT>(rd, to, seg, p2[a - LF::Q]);
       });
     };
     // Stores by every wave, those of lanes without a second-step node out of
@@ -285,7 +280,7 @@ static hipError_t launch_paired_of(lbm_handle* h, const void* src, void* dst, hi
     TwoStep ts;
     two_step_plan(g, TY, h->cu_count, ts);
     auto launch = [&](auto nt) {
-      hipLaunchKernelGGL((k_step2<M, T, T, T, decltype(les)::value, decltype(kind)::value, TY, decltype(nt)::value>),
+      hipLaunchKernelGGL((k_step2<M, T, decltype(les)::value, decltype(kind)::value, TY, decltype(nt)::value>),
                          dim3(ts.nblocks), dim3(64 * (TY + 3)), 0, stream, static_cast<const T*>(src),
                          static_cast<T*>(dst), g, phys_of<T>(h), ts);
     };
