@@ -253,8 +253,8 @@ int lbm_checkpoint_load(lbm_handle* h, const void* dev_slot);
  * non-dimensional values) are used as given. step, x_f and mass0/chi_mass0
  * come from the slot's header. The scratch of the diagnostics kernels (span
  * sums of chi, per-block partial sums, a result slot) is a static device
- * array of 32 MiB per GPU, held until the process ends: LBM_ENOMEM if the
- * grid needs more (nx * nz above about 4.1 million). Nothing is allocated.
+ * array of 40 MiB per GPU, held until the process ends: LBM_ENOMEM for grids
+ * that are too large for it (nx * nz above about 4.1 million). Nothing is allocated.
  * Every call on one GPU shares that GPU's array: calls that overlap on one
  * GPU (other host threads, other streams) race and must be serialised by the
  * caller. hip_stream: the stream to run on (NULL = default); synchronises

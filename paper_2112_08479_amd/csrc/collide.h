@@ -121,9 +121,9 @@ LBM_HD void inverse_chimera(const CT* m, CT ux, CT uy, CT uz, CT* g) {
   });
 }
 
-// ---- the lean forms: the same quantities in fewer operations, for the kernels
-// that the vector units bound (the paired steps, whose two collisions per node
-// take 64 % of the time). The moments come from sums over x shared by all of
+// ---- the lean forms: the same quantities in fewer operations, for the paired
+// steps, which make two collisions per node for the traffic of one (the vector
+// units about half busy with them). The moments come from sums over x shared by all of
 // them (67 additions for 190), the transform back shares its two halves (8
 // operations a triple for 10) and leaves out the odd moments that vanish, the
 // scalar's equilibria come in pairs. Their rounding errors are of the same size,

@@ -1,8 +1,5 @@
-// Steps of model 0 in FP64 on grids that take them two at a time: pairs, and the
-// single steps of an odd count. Multiply-adds are contracted within an
-// expression only, not where the optimiser happens to see one, which differs
-// between kernels: the two then round alike, and a run gives the same bits
-// however it is split into calls.
+// Steps of model 0 in FP64 on grids that take them two at a time; contraction as
+// launch_paired_of asks.
 #pragma clang fp contract(on)
 #include "step_kernel.h"
 #include "twostep_kernel.h"

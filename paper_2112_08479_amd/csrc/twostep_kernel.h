@@ -3,12 +3,14 @@
 // A single step is bound by its nine-row pull (about 5.8 of the copy's 6.3 TB/s,
 // the vector units 41 % busy in FP32), so what is left to gain is traffic. The
 // tile of 64 x TY nodes marching in z computes 19 waves of collisions for 16
-// (TY = 8: ten rows and the ring's columns, then eight rows) and reads 1.14
-// times the state. Measured at 1024 x 64 x 128, us per step, single -> paired:
-// cumulant + D3Q7 FP32 391 -> 255, FP64 817 -> 558; cumulant + D3Q27 FP32 661 ->
-// 396, parametrised 663 -> 432; given rates 394 -> 318. The vector units and the
-// phases between the barriers, in which every wave moves data, share the time
-// about evenly (the lean collisions of collide.h took 283 to 255). Measured and
+// (TY = 8: ten rows and the ring's columns, then eight rows) and reads 1.17
+// times the state (1.23 with the D3Q27 scalar). Measured at 1024 x 64 x 128 with
+// LES, us per step, single -> paired: cumulant + D3Q7 FP32 394 -> 255, given rates
+// 393 -> 322, parametrised 394 -> 275, FP64 820 -> 560, 885 -> 652 and 845 -> 594;
+// cumulant + D3Q27 FP32 656 -> 401, 649 -> 488 and 657 -> 433; BGK FP64 599 -> 443.
+// The vector units are 52 % busy (46 % with the D3Q27 scalar, 49 % parametrised);
+// the rest of the time goes to the phases between the barriers, in which every
+// wave moves data (the lean collisions of collide.h took 283 to 255). Measured and
 // not taken: TY = 5 or 3 with two blocks per CU (670 and 890 us per pair against
 // 558), pulling before the first step's collision (579 against 560), half the
 // waves with their two steps in the other order (the registers spill: 612), four
@@ -271,6 +273,12 @@ __global__ __launch_bounds__(64 * (TY + 3), tile_waves<T>()) void k_step2(const 
   }
 }
 
+// Steps of a grid that takes them two at a time: pairs, and the single steps of
+// an odd count. Included by translation units of their own with `#pragma clang fp
+// contract(on)` before the includes: multiply-adds are contracted within an
+// expression only, not where the optimiser happens to see one, which differs
+// between kernels. The two then round alike, and a run gives the same bits
+// however it is split into calls.
 template <int M, typename T>
 static hipError_t launch_paired_of(lbm_handle* h, const void* src, void* dst, hipStream_t stream) {
   const Grid g = grid_of(h);
