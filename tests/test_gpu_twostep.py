@@ -1,10 +1,11 @@
 """Steps taken two at a time against single steps: the same bits.
 
-Single steps are held to the oracle in test_gpu_parity.py; lbm_step takes pairs
-of steps on grids large enough for it, so a run in one call must leave the
-populations that the same number of calls of one step leaves. Grids on and off
-the tile edges (64 nodes in x; 8 rows in FP32, 5 in FP64; a z chunk's end), odd
-step counts, every model, LES and closure.
+lbm_step takes pairs of steps on grids large enough for it, so a run in one call
+must leave the populations that the same number of calls of one step leaves.
+About half of the grids below pair; the others hold single steps to themselves.
+test_gpu_pairs.py has the grids that are asserted to pair and holds their single
+steps to the oracle, as test_gpu_fullsize.py does; those of test_gpu_parity.py
+are too small to pair.
 """
 import numpy as np
 import pytest
