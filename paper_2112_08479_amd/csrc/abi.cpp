@@ -239,8 +239,8 @@ AdjLayout adj_layout(const lbm_config* c, const lbm_params* p, int64_t n_steps, 
   // the other k - 1 (fewer when the run is shorter)
   L.ktraj = (k < n_steps ? k : n_steps) - 1;
   L.overlap = L.nseg >= 2 && L.buf <= kOverlapStateBytes;
-  // the smallest blocks the reverse step takes
-  const int bx = lbm::tile_threads(c->nx, (int64_t)c->ny * c->nz, 1);
+  // the smallest blocks the reverse step takes on any GPU
+  const int bx = lbm::tile_threads(c->nx, (int64_t)c->ny * c->nz, 1, 0);
   const int64_t ablocks = (int64_t)((c->nx + bx - 1) / bx) * c->ny * c->nz;
   const int64_t fblocks = (int64_t)lbm::xblocks(c->nx) * c->ny * std::min(c->nz, 2);
   size_t off = 0;

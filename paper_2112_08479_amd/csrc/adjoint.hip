@@ -359,15 +359,15 @@ __global__ void k_zero(double* p, int64_t n) {
 
 // ---------------------------------------------------------------- launchers
 // The parametrised kernel's LDS holds a column per thread of a full block, so
-// its blocks stay as full as a row allows. The others take the step's blocks, for
-// rows of three waves too: whole rows (192 threads) are faster on a few grids whose
-// rows fill the CUs evenly (100 steps, cumulant + D3Q27 FP32: 185 x 16 x 24 2.99 ms
-// against 3.14, 192 x 16 x 32 3.44 against 3.52) and slower on the others (180 x 24 x
-// 24 4.42 against 3.75, 160 x 40 x 40 8.41 against 7.59, 129 x 30 x 50 7.55 against
-// 7.27; cumulant + D3Q7 FP64 150 x 20 x 60 8.07 against 7.30).
+// its blocks stay as full as a row allows. The others take the step's blocks. Whole
+// rows of three waves (100 steps, whole against one wave at a time) are faster in
+// the same range of rows, cumulant + D3Q7, BGK and + D3Q27 FP32 at 192 x 16 x 32 2.42 ms
+// against 2.48, 1.97 / 2.02 and 3.44 / 3.52, and slower elsewhere: + D3Q27 FP32 180 x 24 x 24
+// 4.42 / 3.75, 160 x 40 x 40 8.41 / 7.59, 129 x 30 x 50 7.55 / 7.27; cumulant + D3Q7 FP64 150 x
+// 20 x 60 8.07 / 7.30 (not at 185 x 16 x 24, + D3Q27 FP32 2.99 / 3.14).
 static int ablock(const lbm_handle* h) {
   if (h->cfg.parametrized) return block_x(h);
-  return tile_threads(h->cfg.nx, (int64_t)h->cfg.ny * h->cfg.nz, 1);
+  return tile_threads(h->cfg.nx, (int64_t)h->cfg.ny * h->cfg.nz, 1, h->cu_count);
 }
 
 int adjoint_blocks(const lbm_handle* h) {

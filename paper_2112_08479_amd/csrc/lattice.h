@@ -200,9 +200,17 @@ LBM_HD void static_for(F&& f);
 // step: 5 waves a row, 19.2 us in blocks of 256, 15.8 in blocks of 64). Grids
 // of few waves go out one by one (128 x 8 x 16 FP64: 5.3 us against 5.6 in
 // pairs).
-LBM_HD int tile_threads(int nx, int64_t rows, int npt) {
+// Rows of three waves stay whole (one node per thread) where they fill the cus
+// compute units two deep, to 85 % and more: 170 x 16 x 31, 496 rows on 256
+// CUs, whole against one wave at a time: cumulant + D3Q27 FP32 +7.6 %, FP64 +10 %,
+// cumulant + D3Q7 FP32 +0.7 %, FP64 +4.2 %, FP16 +2.9 %, BGK +0.2 %; 440 rows +0.2, +13,
+// +1.4, -1.7, +2.8 and +0.9. Just above two deep whole rows lose 3 to 12 % (528 rows), at
+// half of it up to 13 % (280 rows); in between, and at one, three and more blocks per
+// CU, the kernels differ by up to 12 % either way.
+LBM_HD int tile_threads(int nx, int64_t rows, int npt, int cus) {
   const int w = (nx + kXB * npt - 1) / (kXB * npt);
   if (w * rows <= 512) return 64;
+  if (w == 3 && npt == 1 && rows <= 2 * (int64_t)cus && 10 * rows >= 17 * (int64_t)cus) return 3 * kXB;
   return w % 4 == 0 ? 256 : (w % 2 == 0 ? 128 : 64);
 }
 

@@ -250,7 +250,7 @@ __global__ __launch_bounds__(1024) void k_diag_final(const double* __restrict__ 
 hipError_t launch_moments(lbm_handle* h, int dtype, void* rho, void* ux, void* uy, void* uz,
                           void* chi) {
   const Grid g = grid_of(h);
-  const int bx = tile_threads(g.nx, (int64_t)g.ny * g.nz, 1);
+  const int bx = tile_threads(g.nx, (int64_t)g.ny * g.nz, 1, h->cu_count);
   const int nbx = (g.nx + bx - 1) / bx;
   const unsigned blocks = (unsigned)((int64_t)nbx * g.ny * g.nz);
   const double gp = h->prm.g_prime;

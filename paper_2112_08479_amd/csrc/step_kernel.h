@@ -95,7 +95,7 @@ static hipError_t launch_step_npt(lbm_handle* h, const Grid& g, const void* src,
   // take full blocks whatever the row leaves idle.
   const int lanes = (g.nx + NPT - 1) / NPT;
   const int bx = NPT > 1 && !PAIRED ? std::min(kBlock, (lanes + 63) / 64 * 64)
-                                    : tile_threads(g.nx, (int64_t)g.ny * g.nz, NPT);
+                                    : tile_threads(g.nx, (int64_t)g.ny * g.nz, NPT, h->cu_count);
   const int nbx = (g.nx + bx * NPT - 1) / (bx * NPT);
   const unsigned blocks = (unsigned)((int64_t)nbx * g.ny * g.nz);
   const Phys<CT> p = phys_of<CT>(h);
