@@ -199,7 +199,14 @@ LBM_HD void static_for(F&& f);
 // of one, so that no wave of a block is past the row's end (320 x 20 x 40 FP32
 // step: 5 waves a row, 19.2 us in blocks of 256, 15.8 in blocks of 64). Grids
 // of few waves go out one by one (128 x 8 x 16 FP64: 5.3 us against 5.6 in
-// pairs).
+// pairs), but not where the last wave of every row of two or four is nearly empty:
+// one by one those steps take up to 2 us longer, for a reason that is not known.
+// 200 x 10 x 11, whole row against one wave at a time, 50 steps: cumulant + D3Q27 FP32
+// 343 / 432 us, FP64 453 / 449, cumulant + D3Q7 FP32 302 / 349, FP64 356 / 380, FP16 317 /
+// 367, BGK 252 / 288; 72 x 10 x 15 320 / 404, 378 / 435, 277 / 329, 303 / 347, 286 / 355, 248 /
+// 284. It sets in above one wave per CU, ends at 16 lanes exactly, and rows of three
+// and five waves and more have none of it. Up to one wave per CU rows of two waves show
+// a smaller form, to 32 lanes: 90 x 7 x 12 FP32 310 / 329, + D3Q7 277 / 278, FP16 284 / 294.
 // Rows of three waves stay whole (one node per thread) where they fill the cus
 // compute units two deep, to 85 % and more: 170 x 16 x 31, 496 rows on 256
 // CUs, whole against one wave at a time: cumulant + D3Q27 FP32 +7.6 %, FP64 +10 %,
@@ -209,7 +216,12 @@ LBM_HD void static_for(F&& f);
 // CU, the kernels differ by up to 12 % either way.
 LBM_HD int tile_threads(int nx, int64_t rows, int npt, int cus) {
   const int w = (nx + kXB * npt - 1) / (kXB * npt);
-  if (w * rows <= 512) return 64;
+  if (w * rows <= 512) {
+    const int last = nx - (w - 1) * (kXB * npt);  // nodes of a row's last wave
+    if (w == 2 && last <= 32 * npt) return 2 * kXB;
+    if (w == 4 && last <= 16 * npt && cus > 0 && w * rows > cus) return 4 * kXB;
+    return 64;
+  }
   if (w == 3 && npt == 1 && rows <= 2 * (int64_t)cus && 10 * rows >= 17 * (int64_t)cus) return 3 * kXB;
   return w % 4 == 0 ? 256 : (w % 2 == 0 ? 128 : 64);
 }

@@ -19,9 +19,23 @@ int main() {
   want(128, 496, 1, 256, 128);
   want(256, 496, 1, 256, 256);
   want(256, 128, 1, 256, 64);
+  // few waves: whole rows of two and four whose last wave is nearly empty
+  for (int64_t rows : {20, 100, 150, 256}) {
+    for (int nx : {65, 80, 96}) want(nx, rows, 1, 256, 128);
+    for (int nx : {97, 112, 128}) want(nx, rows, 1, 256, 64);
+  }
+  for (int nx : {193, 208}) {
+    want(nx, 72, 1, 256, 256);
+    want(nx, 128, 1, 256, 256);
+    want(nx, 64, 1, 256, 64);
+    want(nx, 128, 1, 0, 64);
+  }
+  for (int nx : {209, 224, 225, 256}) want(nx, 100, 1, 256, 64);
+  want(129, 150, 1, 256, 64);
+  want(257, 90, 1, 256, 64);
   want(576, 496, 1, 256, 64);
   for (int nx = 1; nx <= 512; ++nx)
-    for (int64_t rows : {1, 100, 300, 470, 500, 600, 5000})
+    for (int64_t rows : {1, 30, 70, 100, 128, 200, 256, 300, 470, 500, 600, 5000})
       for (int cus : {64, 256, 304}) {
         const int t = tile_threads(nx, rows, 1, cus), least = tile_threads(nx, rows, 1, 0);
         const int waves = (nx + 63) / 64;
