@@ -352,7 +352,11 @@ def populations_from_central(kappa, u, lat):
     pw = torch.stack([torch.ones_like(d), d, d * d])            # (3 powers, 3 axes, Q, n)
     T = torch.einsum('apn,bpn,cpn->nabcp', pw[:, 0], pw[:, 1], pw[:, 2]).reshape(n, 27, lat.Q)
     rhs = kappa.reshape(27, n).T.unsqueeze(-1)
-    return torch.linalg.solve(T, rhs).squeeze(-1).T
+    lu, piv = torch.linalg.lu_factor(T)
+    phi = torch.linalg.lu_solve(lu, piv, rhs)
+    # one step of iterative refinement: LAPACK builds differ by a few roundings
+    phi = phi + torch.linalg.lu_solve(lu, piv, rhs - T @ phi)
+    return phi.squeeze(-1).T
 
 
 def collide_fcm(phi, chi, u, tau_phi, P, omega_high=1.0):
