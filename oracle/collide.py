@@ -352,11 +352,25 @@ def populations_from_central(kappa, u, lat):
     pw = torch.stack([torch.ones_like(d), d, d * d])            # (3 powers, 3 axes, Q, n)
     T = torch.einsum('apn,bpn,cpn->nabcp', pw[:, 0], pw[:, 1], pw[:, 2]).reshape(n, 27, lat.Q)
     rhs = kappa.reshape(27, n).T.unsqueeze(-1)
-    lu, piv = torch.linalg.lu_factor(T)
-    phi = torch.linalg.lu_solve(lu, piv, rhs)
-    # one step of iterative refinement: LAPACK builds differ by a few roundings
-    phi = phi + torch.linalg.lu_solve(lu, piv, rhs - T @ phi)
-    return phi.squeeze(-1).T
+    phi = torch.linalg.solve(T, rhs).squeeze(-1).T
+    # One step of iterative refinement: LAPACK builds differ by a few roundings,
+    # which the residual holds. T is the product of the three axes' maps, taken in
+    # turn here; the derivative is the solve's.
+    with torch.no_grad():
+        i, j, k = (lat.c + 1).long().T
+        res = torch.empty_like(kappa)
+        res[i, j, k] = phi
+        for axis in range(3):                                    # moments about u
+            a, b, c = res.unbind(axis)
+            p, m, v = 1 - u[axis], 1 + u[axis], u[axis]
+            res = torch.stack([a + b + c, p * c - v * b - m * a, p * p * c + v * v * b + m * m * a], axis)
+        res = kappa - res
+        for axis in range(3):                                    # and back
+            m0, m1, m2 = res.unbind(axis)
+            m1, m2 = m1 + u[axis] * m0, m2 + 2 * u[axis] * m1 + u[axis] ** 2 * m0
+            res = torch.stack([(m2 - m1) / 2, m0 - m2, (m2 + m1) / 2], axis)
+        fix = res[i, j, k]
+    return phi + fix
 
 
 def collide_fcm(phi, chi, u, tau_phi, P, omega_high=1.0):
